@@ -333,7 +333,7 @@ struct cpf_solver {
     // workspace
     unsigned char *ws = nullptr;
     size_t ws_bytes = 0, total = 0;
-    size_t off_dev, off_si, off_opdev, off_hist;
+    size_t off_dev, off_si, off_opdev, off_hist, off_wl;
     hipStream_t stream = nullptr;
     bool bound = false;
     Scalars *hsc = nullptr;     // pinned host mirror of the per-RVE scalars
@@ -552,6 +552,7 @@ static void layout(cpf_solver *s)
     s->off_dev = take(sizeof(RveDev<R>) * n);
     s->off_si = take(sizeof(StepInit) * n);
     s->off_opdev = take(sizeof(RveDev<R>));
+    s->off_wl = take(sizeof(double) * 64 * WL_TAB);
     s->off_hist = take(sizeof(unsigned long long) * (CPF_MAX_HIST_BINS + 2) + sizeof(double) * (CPF_MAX_HIST_BINS + 1));
     s->total = o;
 }
@@ -640,6 +641,52 @@ static bool table1_specializable(const cpf_problem &p)
     return true;
 }
 
+// x lines per block of the x pass.
+static void set_lines(RveHost &h, int L)
+{
+    h.L = L;
+    h.tpbx = L * h.nx;
+    h.nbx = (h.ny * h.nz + L - 1) / L;
+}
+
+// The wave-cooperative x pass: FP64, Table 1 systems, fixed substeps, the
+// implicit regularization; the rest keeps a lane per voxel.  FP32 does too
+// (cpfft_wavelaw.hpp): below 32768 voxels, where CUs are idle, the
+// cooperative law would be faster there as well (16^3 64 / 38 us, 32^3 65 /
+// 44), but a member of a batch has to be computed as in a solve of its own,
+// and in a batch that fills the chip it is slower (48^3 79 / 122).
+static bool wave_xpass_on(const cpf_solver *s)
+{
+    return s->law_spec == LAW_TABLE1 && s->prec == CPF_PREC_FP64 && !(s->opt.rk_tol > 0.0) &&
+           s->opt.reg_mode != CPF_REG_LAGGED;
+}
+
+// Voxels per block of the cooperative law, at most: the x pass takes whole
+// lines of nx voxels.  A block's four waves take its groups of 16 voxels in
+// turn, so its time goes by the groups of one wave, plus about half a group
+// for the transforms and rotations; about 768 blocks are resident (three per
+// CU).  Small problems gain from few voxels per block (every CU has one),
+// large ones from many, and lines that are no multiple of 64 leave waves
+// idle; of the sizes tried the one with the least time by this count is
+// taken (FP64 x pass, 256 and the chosen: 24^3 77 / 58 us, 32^3 91 / 63, 64^3
+// 373 / 350).  By the member's own grid alone, so that it is computed the
+// same in every batch.
+static int wave_block_voxels(long lines, int nx)
+{
+    int best = 256;
+    double least = 1e300;
+    for (int cap : {256, 192, 128, 96, 64}) {
+        const int L = std::max(1, cap / nx);
+        const long blocks = (lines + L - 1) / L;
+        const double t = (double)((blocks + 767) / 768) * (((L * nx + 15) / 16 + 3) / 4 + 0.5);
+        if (t < least) {
+            least = t;
+            best = cap;
+        }
+    }
+    return best;
+}
+
 // Members of a batch share the crystal stiffness, the systems and the law.
 static bool same_material(const cpf_problem &a, const cpf_problem &b)
 {
@@ -671,9 +718,7 @@ static void init_rve(RveHost &h, const cpf_problem &p, int green, int nyquist)
     radix_plan(h.nx, h.px);
     radix_plan(h.ny, h.py);
     radix_plan(h.nz, h.pz);
-    h.L = std::max(1, 256 / h.nx);
-    h.tpbx = h.L * h.nx;
-    h.nbx = (h.ny * h.nz + h.L - 1) / h.L;
+    set_lines(h, std::max(1, 256 / h.nx));
     default_tiles<R>(h);
 }
 
@@ -727,6 +772,9 @@ extern "C" int cpf_batch_create(int n, const cpf_problem *const *probs, const cp
         if (s->prec == CPF_PREC_FP64) init_rve<double>(s->rv[i], *probs[i], o.green, o.nyquist_mode);
         else init_rve<float>(s->rv[i], *probs[i], o.green, o.nyquist_mode);
     }
+    if (wave_xpass_on(s))
+        for (auto &h : s->rv)
+            set_lines(h, std::max(1, wave_block_voxels((long)h.ny * h.nz, h.nx) / h.nx));
     if (s->prec == CPF_PREC_FP64) { layout<double>(s); pass_grids<double>(s); }
     else { layout<float>(s); pass_grids<float>(s); }
     if (o.mu0 > 0) {
@@ -915,9 +963,50 @@ static int zero_state(cpf_solver *s)
     return CPF_OK;
 }
 
+// Matrices of the wave-cooperative law as A operands, one value per lane
+// (lane: matrix row lane % 16, column lane / 16): tab[WL_TAB][64].
+static void wave_law_table(const cpf_problem &p, double *tab)
+{
+    double PC[16][6], H[16][16];
+    const auto present = [&](int sy) { return sy < p.nsys; };
+    for (int a = 0; a < 16; ++a)
+        for (int J = 0; J < 6; ++J) {
+            double t = 0.0;
+            if (present(a))
+                for (int I = 0; I < 6; ++I)
+                    t += (I < 3 ? 1.0 : 2.0) * p.m[6 * a + I] * p.Cv[I * 6 + J] * (J < 3 ? 1.0 : 2.0);
+            PC[a][J] = t;
+        }
+    for (int a = 0; a < 16; ++a)
+        for (int b = 0; b < 16; ++b) {
+            double t = 0.0;
+            if (present(a) && present(b))
+                for (int J = 0; J < 6; ++J) t += PC[a][J] * p.m[6 * b + J];
+            H[a][b] = t;
+        }
+    int row_sys[16];
+    for (int g = 0; g < 4; ++g)
+        for (int r = 0; r < 4; ++r) row_sys[wl_row(g, r)] = wl_sys(g, r);
+    for (int l = 0; l < 64; ++l) {
+        const int row = l % 16, k = l / 16, a = row_sys[row];
+        for (int j = 0; j < 2; ++j) tab[(WL_PC + j) * 64 + l] = 4 * j + k < 6 ? PC[a][4 * j + k] : 0.0;
+        for (int j = 0; j < 4; ++j) {
+            const int b = wl_sys(k, j);
+            tab[(WL_H + j) * 64 + l] = -H[a][b];
+            tab[(WL_PT + j) * 64 + l] = row < 6 && present(b) ? p.m[6 * b + row] : 0.0;
+        }
+    }
+}
+
 template <typename R>
 static int bind_impl(cpf_solver *s)
 {
+    if (wave_xpass_on(s)) {
+        double tab[64 * WL_TAB];
+        wave_law_table(s->rv[0].pb, tab);
+        HIPCHK(hipMemcpyAsync(s->ws + s->off_wl, tab, sizeof tab, hipMemcpyHostToDevice, s->stream));
+        HIPCHK(hipStreamSynchronize(s->stream));
+    }
     for (auto &h : s->rv) {
         const cpf_problem &p = h.pb;
         std::vector<R> Qr(p.Q.size());
@@ -1023,21 +1112,44 @@ static void launch_xiter(cpf_solver *s, const LawP<R> &P)
         const double lim2 = (15.0 * s->opt.rk_tol) * (15.0 * s->opt.rk_tol);
         hipLaunchKernelGGL((k_xpass_iter<R, NS, SPEC, true>), dim3(s->nbx_tot), dim3(256), s->lds_x, s->stream,
                            dptr<RveDev<R>>(s, s->off_dev), (int)s->rv.size(), P, lim2, CPF_RK_MAX_DOUBLINGS);
-    } else if (s->opt.aa_depth > 0) {
-        hipLaunchKernelGGL((k_xpass_iter<R, NS, SPEC, false, true>), dim3(s->nbx_tot), dim3(256), s->lds_x,
-                           s->stream, dptr<RveDev<R>>(s, s->off_dev), (int)s->rv.size(), P, 0.0, 0);
     } else if (s->opt.reg_mode == CPF_REG_LAGGED) {
         hipLaunchKernelGGL((k_xpass_iter<R, NS, SPEC, false, false, true>), dim3(s->nbx_tot), dim3(256),
                            s->lds_x, s->stream, dptr<RveDev<R>>(s, s->off_dev), (int)s->rv.size(), P, 0.0, 0);
+    } else if constexpr (sizeof(R) == 8 && SPEC == LAW_TABLE1) {
+        // the cooperative law's (launch_xiter_any)
+    } else if (s->opt.aa_depth > 0) {
+        hipLaunchKernelGGL((k_xpass_iter<R, NS, SPEC, false, true>), dim3(s->nbx_tot), dim3(256), s->lds_x,
+                           s->stream, dptr<RveDev<R>>(s, s->off_dev), (int)s->rv.size(), P, 0.0, 0);
     } else {
         hipLaunchKernelGGL((k_xpass_iter<R, NS, SPEC, false>), dim3(s->nbx_tot), dim3(256), s->lds_x, s->stream,
                            dptr<RveDev<R>>(s, s->off_dev), (int)s->rv.size(), P, 0.0, 0);
     }
 }
 
+template <int NSL, bool AAM, bool UNI>
+static void launch_xwave(cpf_solver *s, const LawP<double> &P)
+{
+    int nx = 0;
+    for (const auto &h : s->rv) nx = std::max(nx, h.nx);
+    hipLaunchKernelGGL((k_xpass_wave<NSL, AAM, UNI>), dim3(s->nbx_tot), dim3(256), xwave_lds_bytes(nx), s->stream,
+                       dptr<RveDev<double>>(s, s->off_dev), (int)s->rv.size(), P, dptr<double>(s, s->off_wl));
+}
+template <bool AAM>
+static void launch_xwave_any(cpf_solver *s, const LawP<double> &P)
+{
+    if (P.nm1_uni >= 1) s->ns_inst == 12 ? launch_xwave<3, AAM, true>(s, P) : launch_xwave<4, AAM, true>(s, P);
+    else s->ns_inst == 12 ? launch_xwave<3, AAM, false>(s, P) : launch_xwave<4, AAM, false>(s, P);
+}
+
 template <typename R>
 static void launch_xiter_any(cpf_solver *s, const LawP<R> &P)
 {
+    if constexpr (sizeof(R) == 8) {
+        if (wave_xpass_on(s)) {
+            s->opt.aa_depth > 0 ? launch_xwave_any<true>(s, P) : launch_xwave_any<false>(s, P);
+            return;
+        }
+    }
     if (s->law_spec == LAW_TABLE1) {
         if (s->ns_inst == 12) launch_xiter<R, 12, LAW_TABLE1>(s, P);
         else launch_xiter<R, 16, LAW_TABLE1>(s, P);

@@ -15,6 +15,7 @@
 // Plus single-purpose kernels for the component operators and fields.
 #pragma once
 #include "cpfft_device.hpp"
+#include "cpfft_wavelaw.hpp"
 
 namespace cpf {
 
@@ -466,6 +467,179 @@ __global__ __launch_bounds__(256, (xpass_min_blocks<R, SPEC>())) void k_xpass_it
     lds_fft<R, false, 8>(buf, 3 * d.L, d.nx, d.px, twl, tid, nthr);
     if (tid < d.tpbx)
         store_halfspec_pairs(d.spec, buf, d.nx, d.ny, d.nz, d.nkx, d.nhp, d.L, li, x, y, z, valid);
+}
+
+// ---------------------------------------------------------------------------
+// The same pass in FP64 with the wave-cooperative law (Table 1 systems,
+// fixed substeps).  The block's threads do the transforms and the rotations
+// one voxel each; in between its waves integrate the voxels in groups of 16,
+// the strains handed over in LDS.  LDS: the transform lines (idle during the
+// law, when the waves' root-solve lists lie there), H, the strain rows, the
+// twiddles.
+// ---------------------------------------------------------------------------
+static_assert(4 * WL_LIST_BYTES >= 3 * 256 * sizeof(C2<double>), "the transform lines exceed the lists");
+constexpr size_t xwave_lds_bytes(int nx)
+{
+    return 4 * WL_LIST_BYTES + WL_LDS_TAB * 64 * sizeof(double) + WL_ROWS_BYTES + nx * sizeof(C2<double>);
+}
+
+// Strains of one voxel into the crystal frame and the block's rows:
+// x0 = eps_n - ep_n (elastic strain at the start), dx = eps - eps_n.
+__device__ __forceinline__ void wl_enter(double *rc, const double Q[9], const double x0l[6], const double dxl[6])
+{
+    double c[6];
+    rot_to_crystal(Q, x0l, c);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) rc[i * WL_STRIDE] = c[i];
+    rot_to_crystal(Q, dxl, c);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) rc[(6 + i) * WL_STRIDE] = c[i];
+}
+
+// Stress of one voxel from the rows after the law, and its new plastic
+// strain (lab frame) into the trial state.
+__device__ __forceinline__ void wl_leave(const LawP<double> &P, const double *rc, const double Q[9],
+                                         const double *st_in, double *st_out, long nvox, long vox, double sigl[6])
+{
+    double a[6], c[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) a[i] = rc[i * WL_STRIDE];
+    hooke_c<double, LAW_TABLE1>(P.C, a, c);
+    rot_to_lab(Q, c, sigl);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) a[i] = rc[(6 + i) * WL_STRIDE];
+    rot_to_lab(Q, a, c);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) st_out[i * nvox + vox] = st_in[i * nvox + vox] + c[i];
+}
+
+// Blocks per CU that the registers are limited for: three (168 registers; two
+// blocks with 220 took 2.75 ms at 128^3 against 2.22); two with the software
+// power (213).
+template <bool UNI>
+constexpr int xwave_min_blocks()
+{
+    return UNI ? 3 : 2;
+}
+
+template <int NSL, bool AAM, bool UNI>
+__global__ __launch_bounds__(256, (xwave_min_blocks<UNI>())) void k_xpass_wave(
+    const RveDev<double> *__restrict__ rv, int nrve, LawP<double> Parg, const double *__restrict__ tab)
+{
+    const int r = find_rve(rv, nrve, (int)blockIdx.x, 0);
+    const RveDev<double> &d = rv[r];
+    Scalars *sc = d.sc;
+    if (sc->done) return;
+    const LawP<double> &P = Parg;
+    extern __shared__ unsigned char smem_raw[];
+    C2<double> *buf = reinterpret_cast<C2<double> *>(smem_raw);
+    double *tl = reinterpret_cast<double *>(smem_raw + 4 * WL_LIST_BYTES);
+    double *rows = tl + WL_LDS_TAB * 64;
+    C2<double> *twl = reinterpret_cast<C2<double> *>(rows + WL_ROWS * WL_STRIDE);
+    const int tid = threadIdx.x, nthr = blockDim.x;
+    const int first = sc->iter == 0;
+    const int cur = wl_uniform(sc->cur);
+    const int li = tid / d.nx, x = tid - li * d.nx;
+    const int line0 = (blockIdx.x - d.bx0) * d.L;
+    const int line = line0 + li;
+    const bool valid = tid < d.tpbx && line < d.nlines;
+    const int y = valid ? line % d.ny : 0, z = valid ? line / d.ny : 0;
+    const long vox0 = (long)line0 * d.nx, vox = vox0 + tid;
+    const int nv = min(d.L, d.nlines - line0) * d.nx;
+    const double *eps_n = d.eps[cur];
+    double *eps_k = d.eps[1 - cur];
+    const double *st_in = wl_uniform(d.st[cur]);
+    double *st_out = wl_uniform(d.st[1 - cur]);
+    const double dt = wl_uniform(sc->dt);
+    const int M = wl_uniform(sc->M);
+
+    for (int i = tid; i < WL_LDS_TAB * 64; i += nthr) tl[i] = tab[i];
+    for (int i = tid; i < d.nx; i += nthr) twl[i] = d.tw[0][i];
+    double corr[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    const bool aam = AAM && !first;
+    if (!first && !aam) {
+        if (tid < d.tpbx)
+            load_halfspec_pairs(d.spec, buf, d.nx, d.ny, d.nz, d.nkx, d.nhp, d.L, li, x, y, z, valid);
+        __syncthreads();
+        lds_fft<double, true, 8>(buf, 3 * d.L, d.nx, d.px, twl, tid, nthr);
+        if (tid < d.tpbx) {
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                const C2<double> zz = buf[(p * d.L + li) * d.nx + x];
+                corr[2 * p] = zz.x * d.inv_nvox;
+                corr[2 * p + 1] = zz.y * d.inv_nvox;
+            }
+        }
+    }
+    {
+        double x0[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, dx[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        double Q[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        if (valid) {
+            const double *Qrow = d.Qtab + d.labels[vox] * 9;
+            const double *base = first ? eps_n : eps_k;
+#pragma unroll
+            for (int c = 0; c < 6; ++c) {
+                double e1 = base[c * d.nvox + vox];
+                if (!aam) e1 = e1 - corr[c] + sc->dE[c];
+                const double e0 = eps_n[c * d.nvox + vox];
+                eps_k[c * d.nvox + vox] = e1;
+                x0[c] = e0 - st_in[c * d.nvox + vox];
+                dx[c] = e1 - e0;
+            }
+#pragma unroll
+            for (int i = 0; i < 9; ++i) Q[i] = Qrow[i];
+        }
+        wl_enter(rows + tid, Q, x0, dx);
+    }
+    __syncthreads();
+
+    double part[NPX];
+#pragma unroll
+    for (int i = 0; i < NPX; ++i) part[i] = 0.0;
+    const int wave = wl_uniform(tid >> 6);
+    {
+        int nact = 0, nnewt = 0;
+        double vs = 0.0, ft = 0.0;
+        WlItem *list = reinterpret_cast<WlItem *>(smem_raw + wave * WL_LIST_BYTES);
+        for (int v0 = wave * 16; v0 < nv; v0 += 64)
+            wave_law<NSL, UNI>(P, tab, tl, rows, v0, nv, st_in, st_out, d.nvox, vox0, dt, M, list, vs, ft, nact,
+                                  nnewt);
+        const bool one = wl_lane() == 0;
+        part[7] = one ? vs : 0.0;
+        part[8] = one ? ft : 0.0;
+        part[9] = one ? (double)nact : 0.0;
+        part[10] = (double)nnewt;
+    }
+    __syncthreads();
+
+    // the thread's voxel again (opaque to the compiler, which would hold all
+    // of it through the law)
+    const int t1 = 64 * wave + wl_lane();
+    const int li1 = t1 / d.nx, x1 = t1 - li1 * d.nx;
+    const bool valid1 = t1 < d.tpbx && line0 + li1 < d.nlines;
+    double sig[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (valid1) {
+        const double *Qrow = d.Qtab + d.labels[vox0 + t1] * 9;
+        double Q[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) Q[i] = Qrow[i];
+        wl_leave(P, rows + t1, Q, st_in, st_out, d.nvox, vox0 + t1, sig);
+#pragma unroll
+        for (int c = 0; c < 6; ++c) part[c] = (double)sig[c];
+        part[6] = (double)von_mises(sig);
+    }
+    block_sum<NPX, 4>(part, d.part_x + (long)(blockIdx.x - d.bx0) * NPX);
+
+    if (t1 < d.tpbx) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) buf[(p * d.L + li1) * d.nx + x1] = C2<double>{sig[2 * p], sig[2 * p + 1]};
+    }
+    __syncthreads();
+    lds_fft<double, false, 8>(buf, 3 * d.L, d.nx, d.px, twl, t1, nthr);
+    if (t1 < d.tpbx) {
+        const int y1 = valid1 ? (line0 + li1) % d.ny : 0, z1 = valid1 ? (line0 + li1) / d.ny : 0;
+        store_halfspec_pairs(d.spec, buf, d.nx, d.ny, d.nz, d.nkx, d.nhp, d.L, li1, x1, y1, z1, valid1);
+    }
 }
 
 // Forward x transform of 6 real fields (component operator, one RVE).

@@ -330,6 +330,8 @@ struct cpf_solver {
     int y_elems = 0, z_elems = 0;   // largest 6 ny ty and 6 nz tz over the RVEs
     int y_kinds = 0, z_kinds = 0;   // y / z kernels needed: bit 0 fixed-length, bit 1 generic
     size_t lds_x = 0, lds_y = 0, lds_z = 0;
+    double root[2][LAW_ROOT_WORDS] = {}, root_lo[2] = {};   // law_root_tables
+    bool root_ok[2] = {};
     // workspace
     unsigned char *ws = nullptr;
     size_t ws_bytes = 0, total = 0;
@@ -497,7 +499,7 @@ static void pass_grids(cpf_solver *s)
 {
     s->nbx_tot = s->nby_tot = s->nbz_tot = 0;
     // x pass: FFT buffer, then the law's per-thread work area
-    s->lds_x = xfft_lds_bytes<R>() + law_lds_bytes_ns<R>(s->ns_inst);
+    s->lds_x = xpass_lds_bytes<R>(s->ns_inst);
     s->lds_y = s->lds_z = 0;
     s->y_elems = s->z_elems = 0;
     s->y_kinds = s->z_kinds = 0;
@@ -661,6 +663,31 @@ static bool wave_xpass_on(const cpf_solver *s)
            s->opt.reg_mode != CPF_REG_LAGGED;
 }
 
+// The tables of root_solve (FP32): G = min(X, X/n) - Y with the root Y of
+// log2(2^Y + 2^(nY)) = X by bisection, and log2 of the crossover overstress
+// o* = (K^n / eta)^(1/(n-1)).  Close to n = 1, where the crossover moves
+// away, the families go without.
+static void law_root_tables(cpf_solver *s)
+{
+    const cpf_problem &p = s->rv[0].pb;
+    for (int f = 0; f < 2; ++f) {
+        const cpf_law &L = p.law[f];
+        s->root_ok[f] = p.eta > 0.0 && L.K > 0.0 && L.n >= 1.5;
+        if (!s->root_ok[f]) continue;
+        s->root_lo[f] = (L.n * log2(L.K) - log2(p.eta)) / (L.n - 1.0);
+        for (int i = 0; i < LAW_ROOT_WORDS; ++i) {
+            const int k = i - LAW_ROOT_MID;
+            const double X = k > 0 ? 0.25 * k : 0.5 * k / (L.n - 1.0), m = X < X / L.n ? X : X / L.n;
+            double a = m - 1.0, b = m;
+            for (int it = 0; it < 40; ++it) {
+                const double Y = 0.5 * (a + b);
+                (log2(exp2(Y) + exp2(L.n * Y)) > X ? b : a) = Y;
+            }
+            s->root[f][i] = m - 0.5 * (a + b);
+        }
+    }
+}
+
 // Voxels per block of the cooperative law, at most: the x pass takes whole
 // lines of nx voxels.  A block's four waves take its groups of 16 voxels in
 // turn, so its time goes by the groups of one wave, plus about half a group
@@ -775,6 +802,7 @@ extern "C" int cpf_batch_create(int n, const cpf_problem *const *probs, const cp
     if (wave_xpass_on(s))
         for (auto &h : s->rv)
             set_lines(h, std::max(1, wave_block_voxels((long)h.ny * h.nz, h.nx) / h.nx));
+    if (s->prec != CPF_PREC_FP64) law_root_tables(s);
     if (s->prec == CPF_PREC_FP64) { layout<double>(s); pass_grids<double>(s); }
     else { layout<float>(s); pass_grids<float>(s); }
     if (o.mu0 > 0) {
@@ -878,13 +906,13 @@ extern "C" int cpf_solver_set_graph(cpf_solver *s, int iters_per_launch)
     return CPF_OK;
 }
 
-// Newton stops when the last step is below rtol times the root.  From
-// above the root the iteration converges quadratically, and the relative
-// error left after that step is about (n - 1)/2 times the square of the
-// step (4.5 rtol^2 at n = 10): 1e-6 in FP32, the fixed point's own
-// tolerance in that precision, and 1e-12 in FP64, two orders below the
-// 1e-10 to which FP64 runs are held.
-constexpr double NEWTON_RTOL_F32 = 4.7e-4;
+// A root solve stops when the last step is below rtol times the root.  In
+// FP64 (Newton) the relative error left after that step is about (n - 1)/2
+// times the square of the step (4.5 rtol^2 at n = 10): 1e-12, two orders
+// below the 1e-10 to which FP64 runs are held.  In FP32 (Halley) it is
+// about (n^2 - 1)/12 times the cube of the step: 1.1e-7 at n = 10, the
+// precision itself.
+constexpr double NEWTON_RTOL_F32 = 2.4e-3;
 constexpr double NEWTON_RTOL_F64 = 4.7e-7;
 
 template <typename R>
@@ -911,6 +939,7 @@ static LawP<R> make_law(const cpf_solver *s)
     for (int f = 0; f < 2; ++f) {
         const cpf_law &L = p.law[f];
         FamP<R> F;
+        memset(&F, 0, sizeof F);
         F.QL = R(L.Q * L.q_latent);
         F.QD = R(L.Q * (L.q_self - L.q_latent));
         F.bl2e = R(L.b * 1.442695040888963407359924681001892137);
@@ -919,6 +948,10 @@ static LawP<R> make_law(const cpf_solver *s)
         F.n = R(L.n); F.inv_n = R(1.0 / L.n); F.nm1 = R(L.n - 1.0);
         F.nm1_int = (L.n == floor(L.n) && L.n >= 1.0 && L.n <= 64.0) ? (int)L.n - 1 : -1;
         F.Q = R(L.Q); F.b = R(L.b); F.qs = R(L.q_self); F.ql = R(L.q_latent);
+        if (sizeof(R) == 4) {
+            F.lo = R(s->root_lo[f]); F.lok = R(s->root_lo[f] - log2(L.K)); F.inv_nm1 = R(1.0 / (L.n - 1.0));
+            for (int i = 0; i < LAW_ROOT_WORDS; ++i) P.root[f * LAW_ROOT_WORDS + i] = R(s->root[f][i]);
+        }
         (f ? P.ft : P.fs) = F;
     }
     P.Kc_gT = R(p.Kc * p.gT); P.fm = R(p.fm); P.inv_gT = R(1.0 / p.gT);
@@ -933,6 +966,7 @@ static LawP<R> make_law(const cpf_solver *s)
     // Newton passes mix the families of different lanes)
     bool has[2] = {false, false};
     for (int sy = 0; sy < p.nsys; ++sy) has[p.fam[sy] ? 1 : 0] = true;
+    P.root_ok = (!has[0] || s->root_ok[0]) && (!has[1] || s->root_ok[1]);
     P.nm1_uni = -1;
     for (int f = 0; f < 2; ++f) {
         if (!has[f]) continue;
@@ -1959,7 +1993,7 @@ static void launch_law_adj(cpf_solver *s, const AdjArgs<R> &a, int what)
     const RveHost &h = s->rv[0];
     const dim3 grid((h.nvox + 255) / 256), block(256);
     const LawP<R> P = make_law<R>(s);
-    const size_t lds = law_lds_bytes<R, NS>() + law_items_bytes<R>();
+    const size_t lds = law_lds_bytes<R, NS, true>() + law_items_bytes<R>();
     if (what == 0) hipLaunchKernelGGL((k_law_record<R, NS, SPEC>), grid, block, lds, s->stream, a, P);
     else if (what == 1) hipLaunchKernelGGL((k_law_vjp<R, NS, SPEC, VJP_GA>), grid, block, 0, s->stream, a, P);
     else hipLaunchKernelGGL((k_law_vjp<R, NS, SPEC, VJP_F>), grid, block, 0, s->stream, a, P);

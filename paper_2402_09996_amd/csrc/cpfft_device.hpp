@@ -621,8 +621,14 @@ struct FamP {
     R c, d;    // kinematic hardening
     R K, invK, n, inv_n, nm1;
     int nm1_int;   // n - 1 when n is an integer in [1, 64], else -1
+    R lo, lok, inv_nm1;   // FP32: log2 o*, log2 (o*/K) (root_solve), 1/(n - 1)
     R Q, b, qs, ql;   // raw values for the reverse mode
 };
+
+// Per family: the constants of the Norton rate, and in FP32 the table of
+// root_solve.
+constexpr int LAW_FAM_WORDS = 8;
+constexpr int LAW_ROOT_WORDS = 64, LAW_ROOT_MID = 20;
 
 template <typename R>
 struct LawP {
@@ -639,6 +645,8 @@ struct LawP {
                           // n in [1, 64] (a wave-uniform exponent), else -1
     R tau0k[3];           // FP32 LAW_TABLE1: initial resistance per kind of
                           // Table 1 system (ordinary, superdislocation, twin)
+    int root_ok;          // FP32: the families present have tables of root_solve
+    R root[sizeof(R) == 4 ? 2 * LAW_ROOT_WORDS : 1];   // FP32: slip, twin (root_solve)
 };
 
 // Math in the working precision.  FP32 uses the hardware transcendental
@@ -945,7 +953,7 @@ __device__ __forceinline__ void law_fence() { asm volatile("" ::: "memory"); }
 template <typename R>
 struct LawLds {
     R *o;       // [NS] overstress, then rate
-    R *y;       // [NS] Newton roots (warm starts)
+    R *y;       // [NS] Newton roots (FP64: warm starts; FP32: only if kept)
     R *e;       // [12] start and end strain of the load step
     R *fam;     // [2][LAW_FAM_WORDS] Norton constants of the slip and twin
                 // families, one copy per block
@@ -955,10 +963,10 @@ struct LawLds {
     R *tau0;           // [NS] initial resistances, one copy per block (FP64)
 };
 
-// The Newton solves of a stage are balanced over the lanes of a wave: the
-// active systems of all lanes go to a list of 16-bit items (owner lane,
-// system, warm-start bit), and the wave's active lanes take the items in
-// turn, so a stage needs ceil(items / lanes) passes instead of the largest
+// The root solves of a stage are balanced over the lanes of a wave: the
+// active systems of all lanes go to a list of 16-bit items (FP64: owner
+// lane, system, warm-start bit; FP32: place of the system's overstress in
+// the block's rows), and the wave's active lanes take the items in turn, so a stage needs ceil(items / lanes) passes instead of the largest
 // count of one lane.  Up to law_items_q systems of a lane go to the list
 // (the rest, rare, are solved by their own lane afterwards).  Per wave:
 // the items, then the twin rate prefactor A of each lane (it depends on
@@ -966,7 +974,7 @@ struct LawLds {
 template <typename R>
 constexpr int law_items_q()
 {
-    return sizeof(R) == 4 ? 10 : 16;
+    return 16;
 }
 template <typename R>
 constexpr size_t law_items_wave_bytes()
@@ -983,12 +991,10 @@ constexpr size_t law_items_bytes()
 // The Newton passes take the constants of each lane's family from a small
 // table in LDS instead of selecting every one of them between two scalar
 // registers (two instructions each: a scalar source must be moved to a
-// vector register first).  Per family: K, 1/K, n, 1/n, n - 1, the integer
-// exponent (as a value of R; FP64 only) and two words of padding (16-byte
-// aligned rows).  One table per block (64 bytes in FP32): three FP32 law
-// blocks per CU leave no room for a table per wave in the 160 KB of LDS.
-constexpr int LAW_FAM_WORDS = 8;
-
+// vector register first).  Per family (16-byte aligned rows), FP64: K, 1/K,
+// n, 1/n, n - 1, the integer exponent; FP32: K, n, 1/n, n - 1, log2 of the
+// crossover overstress o*, of o*/K, n (n - 1)/2, 1/(n - 1), then the root
+// tables.  One table per block.
 // Register relief through the LDS work area: the hardening terms within a
 // stage are parked there in FP64 (FP32 keeps them in registers), and the
 // strain path of the step in both precisions, except in FP64 beyond 16
@@ -1015,17 +1021,19 @@ constexpr int law_e_rows(int ns)
     return law_park_e_ns<R>(ns) ? 12 : 0;
 }
 
-// Bytes of the law's LDS work area of a 256-thread block (2 NS words and the
-// strain rows per thread: 44 KB in FP32 at NS = 16), then the family table.
+// Bytes of the law's LDS work area of a 256-thread block (2 NS words, in
+// FP32 NS unless the roots are kept, and the strain rows per thread: 28 KB
+// in FP32 at NS = 16), then the family table.
 template <typename R>
-constexpr size_t law_lds_bytes_ns(int ns)
+constexpr size_t law_lds_bytes_ns(int ns, bool keep = sizeof(R) == 8)
 {
-    return ((2 * (size_t)ns + law_e_rows<R>(ns)) * 256 + 2 * LAW_FAM_WORDS + ns) * sizeof(R);
+    return (((keep ? 2 : 1) * (size_t)ns + law_e_rows<R>(ns)) * 256 + 2 * LAW_FAM_WORDS +
+            (sizeof(R) == 4 ? 2 * LAW_ROOT_WORDS : ns)) * sizeof(R);
 }
-template <typename R, int NS>
+template <typename R, int NS, bool KEEP = sizeof(R) == 8>
 constexpr size_t law_lds_bytes()
 {
-    return law_lds_bytes_ns<R>(NS);
+    return law_lds_bytes_ns<R>(NS, KEEP);
 }
 
 // Fill the block's family table and, in FP64, its table of initial
@@ -1053,11 +1061,27 @@ __device__ __forceinline__ void law_fam_store(const LawP<R> &P, const LawLds<R> 
     for (int f = 0; f < 2; ++f) {
         R *t = W.fam + f * LAW_FAM_WORDS;
         t[0] = F[f]->K;
-        t[1] = F[f]->invK;
-        t[2] = F[f]->n;
-        t[3] = F[f]->inv_n;
-        t[4] = F[f]->nm1;
-        if constexpr (sizeof(R) == 8) t[5] = R(F[f]->nm1_int);
+        if constexpr (sizeof(R) == 8) {
+            t[1] = F[f]->invK;
+            t[2] = F[f]->n;
+            t[3] = F[f]->inv_n;
+            t[4] = F[f]->nm1;
+            t[5] = R(F[f]->nm1_int);
+        } else {
+            t[1] = F[f]->n;
+            t[2] = F[f]->inv_n;
+            t[3] = F[f]->nm1;
+            t[4] = F[f]->lo;
+            t[5] = F[f]->lok;
+            t[6] = R(0.5) * F[f]->n * F[f]->nm1;
+            t[7] = F[f]->inv_nm1;
+        }
+    }
+    if constexpr (sizeof(R) == 4) {
+        const uint64_t ex = __ballot(1);
+        for (int i = __builtin_amdgcn_mbcnt_hi((uint32_t)(ex >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ex, 0u));
+             i < 2 * LAW_ROOT_WORDS; i += __popcll(ex))
+            W.fam[2 * LAW_FAM_WORDS + i] = P.root[i];
     }
 }
 
@@ -1072,48 +1096,89 @@ __device__ __forceinline__ void law_fam_store(const LawP<R> &P, const LawLds<R> 
 // root gives g without another power.  A lane stops at |step| <= rtol y or
 // after 40 iterations (the loop is not unrolled: an unrolled loop leaves a
 // long chain of exec-mask restores at every exit).  yw receives the root.
-template <typename R>
-__device__ __forceinline__ R newton_solve(R o, R A, R etaA, R inv_etaA, const R *fam, const LawP<R> &P, R &yw,
-                                          int &nnewt)
+// FP64 (FP32: root_solve).
+__device__ __forceinline__ double newton_solve(double o, double A, double etaA, double inv_etaA, const double *fam,
+                                               const LawP<double> &P, double &yw, int &nnewt)
 {
-    const R K = fam[0], invK = fam[1], n = fam[2], inv_n = fam[3], nm1 = fam[4];
-    const int nm1_int = sizeof(R) == 8 ? (int)fam[5] : -1;
-    const R yk = o * invK;
-    R y = yw > R(0) ? (yw < yk ? yw : yk) : R(0);
+    const double K = fam[0], invK = fam[1], n = fam[2], inv_n = fam[3], nm1 = fam[4];
+    const int nm1_int = (int)fam[5];
+    const double yk = o * invK;
+    double y = yw > 0.0 ? (yw < yk ? yw : yk) : 0.0;
     // the cold start only when some lane of the pass has no warm start (a
     // wave vote: most passes are warm after the first stage of a step; the
     // empty asm keeps the block a branch instead of selects after an
     // unconditional log2 and exp2)
-    if (__any(!(yw > R(0)))) {
+    if (__any(!(yw > 0.0))) {
         asm volatile("");
-        R yc;
-        if constexpr (sizeof(R) == 8) {
-            // The start only has to lie above the root: the bound in FP32
-            // (hardware log2/exp2, relative error below 1e-6), raised by
-            // 1e-5, instead of the FP64 library sequences.  An FP32 overflow
-            // gives +inf (start at o/K), an underflow 0 (the first step goes
-            // to o/K); both are upper bounds.
-            const float q = (float)(o * inv_etaA);
-            yc = (double)ex2(lg2(q) * (float)inv_n) * (1.0 + 1e-5);
-        } else {
-            yc = ex2(lg2(o * inv_etaA) * inv_n);
-        }
-        if (!(yw > R(0))) y = yk < yc ? yk : yc;
+        // The start only has to lie above the root: the bound in FP32
+        // (hardware log2/exp2, relative error below 1e-6), raised by 1e-5,
+        // instead of the FP64 library sequences.  An FP32 overflow gives
+        // +inf (start at o/K), an underflow 0 (the first step goes to o/K);
+        // both are upper bounds.
+        const float q = (float)(o * inv_etaA);
+        const double yc = (double)ex2(lg2(q) * (float)inv_n) * (1.0 + 1e-5);
+        if (!(yw > 0.0)) y = yk < yc ? yk : yc;
     }
-    const R etaAn = etaA * n;
+    const double etaAn = etaA * n;
 #pragma unroll 1
     for (int it = 0; it < 40; ++it) {
-        const R yn1 = pow_nm1(y, nm1, nm1_int, P.nm1_uni);
-        const R phi = K * y + etaA * yn1 * y - o;
-        const R dphi = K + etaAn * yn1;
-        const R step = phi * rcp_nr(dphi);
+        const double yn1 = pow_nm1(y, nm1, nm1_int, P.nm1_uni);
+        const double phi = K * y + etaA * yn1 * y - o;
+        const double dphi = K + etaAn * yn1;
+        const double step = phi * rcp_nr(dphi);
         y -= step;
         ++nnewt;
         if (fabs(step) <= P.newton_rtol * y) break;
     }
     yw = y;
-    if (P.eta > R(0)) return (o - K * y) * P.inv_eta;
+    if (P.eta > 0.0) return (o - K * y) * P.inv_eta;
     return A * y * pow_nm1(y, nm1, nm1_int, P.nm1_uni);
+}
+
+// The same rate in FP32, without a start from an earlier root.  With the
+// crossover overstress o* = (K^n / (eta A))^(1/(n-1)), X = log2(o / o*) and
+// Y = log2(K y / o*), the equation is 2^X = 2^Y + 2^(nY): one curve per
+// exponent, Y = min(X, X/n) - G(X).  G, which is 0 away from X = 0, is
+// tabulated (linear in between; in steps of 1/(2 (n-1)) octaves below the
+// crossover and 1/4 above, where its curvature is of that scale).  That
+// leaves y within 2.1e-3 of the root at n = 10 (3.4e-3 at n = 50), so that
+// one step of Halley's method ends nearly every solve (1.000 steps per
+// solve at n = 10): the lanes of a pass are done together.  Warm starts
+// took 1.88 Newton steps on average and 3 or more in some lane of a pass,
+// and the roots a column of LDS.  The law's time is the serial chain of a
+// wave (three waves per SIMD): the FP32 x pass at 128^3 went from 823 to
+// 703 us.  Families without a table (root_ok) start as newton_solve does.
+// fam, tab: the family's constants and table; lo: log2 o* for this A.
+__device__ __forceinline__ float root_solve(float o, float A, float etaA, float lo, const float *fam,
+                                            const float *tab, const LawP<float> &P, float &y, int &nnewt)
+{
+    const float K = fam[0], n = fam[1], inv_n = fam[2], nm1 = fam[3], c = fam[6];
+    float b;
+    if (P.root_ok) {
+        const float X = lg2(o) - lo;
+        const float u = fminf(fmaxf(X * (X > 0.f ? 4.f : 2.f * nm1) + float(LAW_ROOT_MID), 0.f),
+                              float(LAW_ROOT_WORDS) - 1.01f);
+        const int i = (int)u;
+        const float Y = fminf(X, X * inv_n) - (tab[i] + __builtin_amdgcn_fractf(u) * (tab[i + 1] - tab[i]));
+        y = ex2(Y + (lo - fam[4] + fam[5]));
+        b = ex2(n * Y + lo);
+    } else {
+        const float yk = fdiv(o, K), yc = ex2(lg2(fdiv(o, etaA)) * inv_n);
+        y = yk < yc ? yk : yc;
+        b = etaA * ex2(n * lg2(y));
+    }
+    float rel;
+    for (int it = 0;;) {
+        const float Ky = K * y, r = rcp_nr(Ky + n * b);
+        const float u = ((Ky + b) - o) * r;
+        rel = u * rcp_nr(1.f - u * (c * b * r));
+        y -= y * rel;
+        ++nnewt;
+        if (!(fabsf(rel) > P.newton_rtol) || ++it >= 40) break;
+        b = etaA * ex2(nm1 * lg2(y)) * y;
+    }
+    if (P.eta > 0.f) return (o - K * y) * P.inv_eta;
+    return A * y * ex2(nm1 * lg2(y));
 }
 
 // One RK4 stage of the internal variables in the crystal frame.  Inputs:
@@ -1126,8 +1191,8 @@ __device__ __forceinline__ R newton_solve(R o, R A, R etaA, R inv_etaA, const R 
 // active in a given lane), so instead of one divergent solve per system,
 // every lane takes its own next active system in each pass of the solve
 // loop.  Overstresses go to the thread's LDS column, rates and roots come
-// back through it; warm holds the systems whose root from the previous
-// stage is a valid warm start.
+// back through it; warm receives the active systems, whose roots are the
+// FP64 warm starts of the next stage.
 //
 // Lagged regularization (LAG): instead of raising the resistance by eta
 // times the rate being solved for, each system's resistance is raised by
@@ -1261,7 +1326,8 @@ __device__ __forceinline__ void rk_stage(const LawP<R> &P, const R e[6], R (&tep
         while (m) {
             const int sy = __builtin_ctz(m);
             m &= m - 1u;
-            W.items[k++] = (uint16_t)((lane << 6) | (sy << 1) | ((warm >> sy) & 1u));
+            W.items[k++] = sizeof(R) == 8 ? (uint16_t)((lane << 6) | (sy << 1) | ((warm >> sy) & 1u))
+                                          : (uint16_t)(sy * W.ls + (int)threadIdx.x);
         }
     }
     W.aw[lane] = Atw;
@@ -1269,29 +1335,45 @@ __device__ __forceinline__ void rk_stage(const LawP<R> &P, const R e[6], R (&tep
     const uint64_t ex = __ballot(1);
     const int nlanes = __popcll(ex);
     const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(ex >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ex, 0u));
-    R *const o_wave = W.o - lane;   // column of lane l: o_wave + l
-    R *const y_wave = W.y - lane;
+    [[maybe_unused]] R *const o_wave = W.o - lane;   // column of lane l: o_wave + l
+    [[maybe_unused]] R *const y_wave = W.y - lane;
     for (int base = 0; base < total; base += nlanes) {
         const int idx = base + rank;
         if (idx < total) {
-            const uint32_t it = W.items[idx];
-            const int owner = (int)(it >> 6), sy = (int)((it >> 1) & 31u);
-            const bool tw = SPEC == LAW_TABLE1 ? sy >= 12 : ((P.twin_mask >> sy) & 1u) != 0u;
-            R *const po = o_wave + owner + sy * W.ls;
-            R *const py = y_wave + owner + sy * W.ls;
-            const R os = *po;
-            const R yprev = *py;
-            R yw = (it & 1u) ? yprev : R(0);
-            R A = R(1), etaA = P.eta, inv_etaA = P.inv_eta;
-            if (tw) {
-                A = W.aw[owner];
-                etaA = P.eta * A;
-                if (P.twin_mode) inv_etaA = fdiv(R(1), etaA);
+            const int it = W.items[idx];
+            if constexpr (sizeof(R) == 4) {
+                const bool tw = SPEC == LAW_TABLE1 ? it >= 12 * W.ls : ((P.twin_mask >> (it / W.ls)) & 1u) != 0u;
+                R *const po = W.o - (int)threadIdx.x + it;
+                const R os = *po;
+                const R *fam = W.fam + (tw ? LAW_FAM_WORDS : 0);
+                R A = R(1), etaA = P.eta, lo = fam[4], y;
+                if (tw) {
+                    A = W.aw[it & 63];
+                    etaA = P.eta * A;
+                    lo -= lg2(A) * fam[7];
+                }
+                const R g = root_solve(fabs(os), A, etaA, lo, fam,
+                                       W.fam + 2 * LAW_FAM_WORDS + (tw ? LAW_ROOT_WORDS : 0), P, y, nnewt);
+                if (W.y) W.y[it - (int)threadIdx.x] = y;
+                *po = copysign(g, os);
+            } else {
+                const int owner = it >> 6, sy = (it >> 1) & 31;
+                const bool tw = SPEC == LAW_TABLE1 ? sy >= 12 : ((P.twin_mask >> sy) & 1u) != 0u;
+                R *const po = o_wave + owner + sy * W.ls;
+                R *const py = y_wave + owner + sy * W.ls;
+                const R os = *po;
+                const R yprev = *py;
+                R yw = (it & 1) ? yprev : R(0);
+                R A = R(1), etaA = P.eta, inv_etaA = P.inv_eta;
+                if (tw) {
+                    A = W.aw[owner];
+                    etaA = P.eta * A;
+                    if (P.twin_mode) inv_etaA = fdiv(R(1), etaA);
+                }
+                const R g = newton_solve(fabs(os), A, etaA, inv_etaA, W.fam + (tw ? LAW_FAM_WORDS : 0), P, yw, nnewt);
+                *py = yw;
+                *po = os < R(0) ? -g : g;
             }
-            const R g = newton_solve<R>(fabs(os), A, etaA, inv_etaA, W.fam + (tw ? LAW_FAM_WORDS : 0), P, yw,
-                                        nnewt);
-            *py = yw;
-            *po = os < R(0) ? -g : g;
         }
     }
     __builtin_amdgcn_wave_barrier();
@@ -1302,13 +1384,18 @@ __device__ __forceinline__ void rk_stage(const LawP<R> &P, const R e[6], R (&tep
             const int sy = __builtin_ctz(rem);
             rem &= rem - 1u;
             const bool tw = SPEC == LAW_TABLE1 ? sy >= 12 : ((P.twin_mask >> sy) & 1u) != 0u;
-            const R os = W.o[sy * W.ls];
-            const R yprev = W.y[sy * W.ls];
-            R yw = ((warm >> sy) & 1u) ? yprev : R(0);
-            const R g = newton_solve<R>(fabs(os), tw ? Atw : R(1), tw ? etaAtw : P.eta,
-                                        tw ? inv_etaAtw : P.inv_eta, W.fam + (tw ? LAW_FAM_WORDS : 0), P, yw,
-                                        nnewt);
-            W.y[sy * W.ls] = yw;
+            const R os = W.o[sy * W.ls], A = tw ? Atw : R(1), etaA = tw ? etaAtw : P.eta;
+            const R *fam = W.fam + (tw ? LAW_FAM_WORDS : 0);
+            R g, y;
+            if constexpr (sizeof(R) == 4) {
+                g = root_solve(fabs(os), A, etaA, tw ? fam[4] - lg2(A) * fam[7] : fam[4], fam,
+                               W.fam + 2 * LAW_FAM_WORDS + (tw ? LAW_ROOT_WORDS : 0), P, y, nnewt);
+            } else {
+                const R yprev = W.y[sy * W.ls];
+                y = ((warm >> sy) & 1u) ? yprev : R(0);
+                g = newton_solve(fabs(os), A, etaA, tw ? inv_etaAtw : P.inv_eta, fam, P, y, nnewt);
+            }
+            if (W.y) W.y[sy * W.ls] = y;
             W.o[sy * W.ls] = os < R(0) ? -g : g;
         }
     }

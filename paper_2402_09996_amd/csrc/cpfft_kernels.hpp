@@ -325,32 +325,46 @@ constexpr int xpass_min_blocks()
 }
 
 // The law's LDS work area of this thread inside a 256-thread block's
-// dynamic LDS, after `offset` bytes used by the kernel itself: 2 NS words
-// per thread (plus 12 when the strain path is parked), column-major
-// (compile-time stride: plain shifts), then the family table.
-template <typename R, int NS, int BD = 256>
+// dynamic LDS, after `offset` bytes used by the kernel itself: NS words per
+// thread, NS more for the roots (KEEP: FP64, and the adjoint's record), 12
+// when the strain path is parked, column-major (compile-time stride: plain
+// shifts), then the family table.
+template <typename R, int NS, bool KEEP = sizeof(R) == 8, int BD = 256>
 __device__ __forceinline__ LawLds<R> law_lds(unsigned char *smem, size_t offset, size_t items_offset)
 {
     R *base = reinterpret_cast<R *>(smem + offset);
     const int t = threadIdx.x;
-    R *fam = base + (2 * NS + law_e_rows<R>(NS)) * BD;
+    constexpr int rows = (KEEP ? 2 : 1) * NS;
+    R *fam = base + (rows + law_e_rows<R>(NS)) * BD;
     unsigned char *iw = smem + items_offset + (t >> 6) * law_items_wave_bytes<R>();
     uint16_t *items = reinterpret_cast<uint16_t *>(iw);
     R *aw = reinterpret_cast<R *>(iw + 64 * law_items_q<R>() * 2);
-    return LawLds<R>{base + t, base + NS * BD + t, base + 2 * NS * BD + t, fam, BD, items, aw,
+    return LawLds<R>{base + t, KEEP ? base + NS * BD + t : nullptr, base + rows * BD + t, fam, BD, items, aw,
                      fam + 2 * LAW_FAM_WORDS};
 }
 
 // Bytes of the x pass FFT area in dynamic LDS: 3 complex lines of up to
-// 256 points, then the twiddles of the line length.  The lines are free
-// while the law runs, and hold its Newton item lists then.
+// 256 points, then the twiddles of the line length.  In FP64 the lines hold
+// the law's item lists while it runs; FP32 has its lists after the law's
+// work area (9 KB, and its lines are 6).
 template <typename R>
 constexpr size_t xfft_lds_bytes()
 {
     return (3 * 256 + 256) * sizeof(C2<R>);
 }
-static_assert(law_items_bytes<float>() <= 3 * 256 * sizeof(C2<float>), "Newton items exceed the FFT lines");
 static_assert(law_items_bytes<double>() <= 3 * 256 * sizeof(C2<double>), "Newton items exceed the FFT lines");
+
+template <typename R>
+constexpr size_t xpass_lds_bytes(int ns)
+{
+    return xfft_lds_bytes<R>() + law_lds_bytes_ns<R>(ns) + (sizeof(R) == 4 ? law_items_bytes<R>() : 0);
+}
+template <typename R, int NS>
+__device__ __forceinline__ LawLds<R> xpass_law_lds(unsigned char *smem)
+{
+    return law_lds<R, NS>(smem, xfft_lds_bytes<R>(),
+                          sizeof(R) == 4 ? xfft_lds_bytes<R>() + law_lds_bytes<R, NS>() : 0);
+}
 
 // LAG: the lagged regularization (d.lag holds the raises of the step).
 template <typename R, int NS, int SPEC, bool ADAPT = false, bool AAM = false, bool LAG = false>
@@ -426,20 +440,20 @@ __global__ __launch_bounds__(256, (xpass_min_blocks<R, SPEC>())) void k_xpass_it
             if (first)
                 voxel_law_probe<R, NS, SPEC>(P, d.Qtab + lab * 9, e0, e1, d.st[cur], &d.st[1 - cur], d.nvox, vox,
                                              R(sc->dt), sc->M, rk_lim2, rk_maxd, d.mv + vox, sig, v, nact, nnewt,
-                                             law_lds<R, NS>(smem_raw, xfft_lds_bytes<R>(), 0));
+                                             xpass_law_lds<R, NS>(smem_raw));
             else
                 voxel_law<R, NS, SPEC>(P, d.Qtab + lab * 9, e0, e1, d.st[cur], &d.st[1 - cur], d.nvox, vox,
                                        R(sc->dt), sc->M << d.mv[vox], sig, v, nact, nnewt,
-                                       law_lds<R, NS>(smem_raw, xfft_lds_bytes<R>(), 0));
+                                       xpass_law_lds<R, NS>(smem_raw));
         } else if constexpr (LAG) {
             voxel_law<R, NS, SPEC, true>(P, d.Qtab + lab * 9, e0, e1, d.st[cur], &d.st[1 - cur], d.nvox, vox,
                                          R(sc->dt), sc->M, sig, v, nact, nnewt,
-                                         law_lds<R, NS>(smem_raw, xfft_lds_bytes<R>(), 0),
+                                         xpass_law_lds<R, NS>(smem_raw),
                                          LagRef<R>{d.lag + vox, d.nvox});
         } else {
             voxel_law<R, NS, SPEC>(P, d.Qtab + lab * 9, e0, e1, d.st[cur], &d.st[1 - cur], d.nvox, vox,
                                    R(sc->dt), sc->M, sig, v, nact, nnewt,
-                                   law_lds<R, NS>(smem_raw, xfft_lds_bytes<R>(), 0));
+                                   xpass_law_lds<R, NS>(smem_raw));
         }
         part[9] = (double)nact;
         part[10] = (double)nnewt;

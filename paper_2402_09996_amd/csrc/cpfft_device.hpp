@@ -2,6 +2,7 @@
 // LDS-resident mixed-radix (2,3,4,8) Stockham FFT, the regularized
 // Meric-Cailletaud rate with RK4 substepping, and FP64 block reductions.
 #pragma once
+#include <type_traits>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -1149,36 +1150,59 @@ __device__ __forceinline__ double newton_solve(double o, double A, double etaA, 
 // wave (three waves per SIMD): the FP32 x pass at 128^3 went from 823 to
 // 703 us.  Families without a table (root_ok) start as newton_solve does.
 // fam, tab: the family's constants and table; lo: log2 o* for this A.
-__device__ __forceinline__ float root_solve(float o, float A, float etaA, float lo, const float *fam,
-                                            const float *tab, const LawP<float> &P, float &y, int &nnewt)
+struct RootIn {
+    float o, A, etaA, lo;
+    const float *fam, *tab;
+};
+// NI systems at once, so that their chains of loads and hardware powers
+// overlap.
+template <int NI>
+__device__ __forceinline__ void root_solve(const RootIn (&q)[NI], const LawP<float> &P, float (&y)[NI], float (&g)[NI])
 {
-    const float K = fam[0], n = fam[1], inv_n = fam[2], nm1 = fam[3], c = fam[6];
-    float b;
+    float b[NI], rel[NI], worst = 0.f;
     if (P.root_ok) {
-        const float X = lg2(o) - lo;
-        const float u = fminf(fmaxf(X * (X > 0.f ? 4.f : 2.f * nm1) + float(LAW_ROOT_MID), 0.f),
-                              float(LAW_ROOT_WORDS) - 1.01f);
-        const int i = (int)u;
-        const float Y = fminf(X, X * inv_n) - (tab[i] + __builtin_amdgcn_fractf(u) * (tab[i + 1] - tab[i]));
-        y = ex2(Y + (lo - fam[4] + fam[5]));
-        b = ex2(n * Y + lo);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            const float X = lg2(q[j].o) - q[j].lo;
+            const float u = fminf(fmaxf(X * (X > 0.f ? 4.f : 2.f * q[j].fam[3]) + float(LAW_ROOT_MID), 0.f),
+                                  float(LAW_ROOT_WORDS) - 1.01f);
+            const float *t = q[j].tab + (int)u;
+            const float Y = fminf(X, X * q[j].fam[2]) - (t[0] + __builtin_amdgcn_fractf(u) * (t[1] - t[0]));
+            y[j] = ex2(Y + (q[j].lo - q[j].fam[4] + q[j].fam[5]));
+            b[j] = ex2(q[j].fam[1] * Y + q[j].lo);
+        }
     } else {
-        const float yk = fdiv(o, K), yc = ex2(lg2(fdiv(o, etaA)) * inv_n);
-        y = yk < yc ? yk : yc;
-        b = etaA * ex2(n * lg2(y));
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            const float yk = fdiv(q[j].o, q[j].fam[0]), yc = ex2(lg2(fdiv(q[j].o, q[j].etaA)) * q[j].fam[2]);
+            y[j] = yk < yc ? yk : yc;
+            b[j] = q[j].etaA * ex2(q[j].fam[1] * lg2(y[j]));
+        }
     }
-    float rel;
-    for (int it = 0;;) {
-        const float Ky = K * y, r = rcp_nr(Ky + n * b);
-        const float u = ((Ky + b) - o) * r;
-        rel = u * rcp_nr(1.f - u * (c * b * r));
-        y -= y * rel;
-        ++nnewt;
-        if (!(fabsf(rel) > P.newton_rtol) || ++it >= 40) break;
-        b = etaA * ex2(nm1 * lg2(y)) * y;
+    const auto step = [&](int j) {
+        const float Ky = q[j].fam[0] * y[j], r = rcp_nr(Ky + q[j].fam[1] * b[j]);
+        const float u = ((Ky + b[j]) - q[j].o) * r;
+        rel[j] = u * rcp_nr(1.f - u * (q[j].fam[6] * b[j] * r));
+        y[j] -= y[j] * rel[j];
+    };
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        step(j);
+        worst = fmaxf(worst, fabsf(rel[j]));
     }
-    if (P.eta > 0.f) return (o - K * y) * P.inv_eta;
-    return A * y * ex2(nm1 * lg2(y));
+    if (__any(worst > P.newton_rtol)) {
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll 1
+            for (int it = 1; it < 40 && fabsf(rel[j]) > P.newton_rtol; ++it) {
+                b[j] = q[j].etaA * ex2(q[j].fam[3] * lg2(y[j])) * y[j];
+                step(j);
+            }
+    }
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+        g[j] = P.eta > 0.f ? (q[j].o - q[j].fam[0] * y[j]) * P.inv_eta
+                           : q[j].A * y[j] * ex2(q[j].fam[3] * lg2(y[j]));
 }
 
 // One RK4 stage of the internal variables in the crystal frame.  Inputs:
@@ -1337,26 +1361,64 @@ __device__ __forceinline__ void rk_stage(const LawP<R> &P, const R e[6], R (&tep
     const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(ex >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ex, 0u));
     [[maybe_unused]] R *const o_wave = W.o - lane;   // column of lane l: o_wave + l
     [[maybe_unused]] R *const y_wave = W.y - lane;
-    for (int base = 0; base < total; base += nlanes) {
-        const int idx = base + rank;
-        if (idx < total) {
-            const int it = W.items[idx];
-            if constexpr (sizeof(R) == 4) {
-                const bool tw = SPEC == LAW_TABLE1 ? it >= 12 * W.ls : ((P.twin_mask >> (it / W.ls)) & 1u) != 0u;
-                R *const po = W.o - (int)threadIdx.x + it;
-                const R os = *po;
-                const R *fam = W.fam + (tw ? LAW_FAM_WORDS : 0);
-                R A = R(1), etaA = P.eta, lo = fam[4], y;
-                if (tw) {
-                    A = W.aw[it & 63];
-                    etaA = P.eta * A;
-                    lo -= lg2(A) * fam[7];
-                }
-                const R g = root_solve(fabs(os), A, etaA, lo, fam,
-                                       W.fam + 2 * LAW_FAM_WORDS + (tw ? LAW_ROOT_WORDS : 0), P, y, nnewt);
-                if (W.y) W.y[it - (int)threadIdx.x] = y;
-                *po = copysign(g, os);
-            } else {
+    if constexpr (sizeof(R) == 4) {
+        // up to three items per lane at once: the chain of a pass (item,
+        // overstress, table, powers, reciprocals) is several times as long as
+        // its issue, and three waves per SIMD do not cover it (FP32 x pass at
+        // 128^3: one item per pass 703 us, two 681, three 679, four 678; the
+        // law alone at 96^3 506, 481, 472, 472)
+        const auto pass = [&](auto NI_, int idx) {
+            constexpr int NI = decltype(NI_)::value;
+            RootIn q[NI];
+            R *po[NI];
+            bool tw[NI], any_tw = false;
+            R os[NI], y[NI], g[NI];
+            int it[NI];
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                // past the end: the lane's first item again
+                const int k = idx + j * nlanes;
+                it[j] = W.items[j == 0 || k < total ? k : idx];
+            }
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                tw[j] = SPEC == LAW_TABLE1 ? it[j] >= 12 * W.ls : ((P.twin_mask >> (it[j] / W.ls)) & 1u) != 0u;
+                any_tw = any_tw || tw[j];
+                po[j] = W.o - (int)threadIdx.x + it[j];
+                os[j] = *po[j];
+                const R *fam = W.fam + (tw[j] ? LAW_FAM_WORDS : 0);
+                q[j] = RootIn{R(fabs(os[j])), R(1), P.eta, fam[4], fam,
+                              W.fam + 2 * LAW_FAM_WORDS + (tw[j] ? LAW_ROOT_WORDS : 0)};
+            }
+            if (__any(any_tw)) {
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+                    if (tw[j]) {
+                        q[j].A = W.aw[it[j] & 63];
+                        q[j].etaA = P.eta * q[j].A;
+                        q[j].lo -= lg2(q[j].A) * q[j].fam[7];
+                    }
+            }
+            root_solve<NI>(q, P, y, g);
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                if (W.y) W.y[it[j] - (int)threadIdx.x] = y[j];
+                *po[j] = copysign(g[j], os[j]);
+            }
+        };
+        int base = 0;
+        for (; base + 2 * nlanes < total; base += 3 * nlanes) pass(std::integral_constant<int, 3>(), base + rank);
+        if (base + nlanes < total) {
+            pass(std::integral_constant<int, 2>(), base + rank);
+            base += 2 * nlanes;
+        }
+        if (base + rank < total) pass(std::integral_constant<int, 1>(), base + rank);
+        nnewt += cnt;
+    } else {
+        for (int base = 0; base < total; base += nlanes) {
+            const int idx = base + rank;
+            if (idx < total) {
+                const int it = W.items[idx];
                 const int owner = it >> 6, sy = (it >> 1) & 31;
                 const bool tw = SPEC == LAW_TABLE1 ? sy >= 12 : ((P.twin_mask >> sy) & 1u) != 0u;
                 R *const po = o_wave + owner + sy * W.ls;
@@ -1388,8 +1450,13 @@ __device__ __forceinline__ void rk_stage(const LawP<R> &P, const R e[6], R (&tep
             const R *fam = W.fam + (tw ? LAW_FAM_WORDS : 0);
             R g, y;
             if constexpr (sizeof(R) == 4) {
-                g = root_solve(fabs(os), A, etaA, tw ? fam[4] - lg2(A) * fam[7] : fam[4], fam,
-                               W.fam + 2 * LAW_FAM_WORDS + (tw ? LAW_ROOT_WORDS : 0), P, y, nnewt);
+                const RootIn q[1] = {{R(fabs(os)), A, etaA, tw ? fam[4] - lg2(A) * fam[7] : fam[4], fam,
+                                      W.fam + 2 * LAW_FAM_WORDS + (tw ? LAW_ROOT_WORDS : 0)}};
+                R y1[1], g1[1];
+                root_solve<1>(q, P, y1, g1);
+                y = y1[0];
+                g = g1[0];
+                ++nnewt;
             } else {
                 const R yprev = W.y[sy * W.ls];
                 y = ((warm >> sy) & 1u) ? yprev : R(0);

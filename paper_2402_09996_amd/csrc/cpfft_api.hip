@@ -688,27 +688,27 @@ static void law_root_tables(cpf_solver *s)
     }
 }
 
-// Voxels per block of the cooperative law, at most: the x pass takes whole
-// lines of nx voxels.  A block's four waves take its groups of 16 voxels in
-// turn, so its time goes by the groups of one wave, plus about half a group
-// for the transforms and rotations; about 768 blocks are resident (three per
-// CU).  Small problems gain from few voxels per block (every CU has one),
-// large ones from many, and lines that are no multiple of 64 leave waves
-// idle; of the sizes tried the one with the least time by this count is
-// taken (FP64 x pass, 256 and the chosen: 24^3 77 / 58 us, 32^3 91 / 63, 64^3
-// 373 / 350).  By the member's own grid alone, so that it is computed the
-// same in every batch.
-static int wave_block_voxels(long lines, int nx)
+// Lines per block of the cooperative law.  A block's four waves take its
+// groups of 16 voxels in turn, so its time goes by the groups of one wave,
+// plus about half a group for the transforms and rotations; about 768 blocks
+// are resident (three per CU).  Small problems gain from few voxels per block
+// (every CU has one; fewer than 64 leave waves without a group), large ones
+// from many, and lines that are no multiple of 64 leave waves idle; the count
+// with the least time is taken (FP64 x pass, 256 voxels and the chosen: 24^3
+// 77 / 58 us, 32^3 91 / 63, 64^3 373 / 350), of equal ones the smallest,
+// which spreads best over the CUs (48^3: 4 lines 190, 3 lines 170 us).  By
+// the member's own grid alone, so that it is computed the same in every
+// batch.
+static int wave_block_lines(long lines, int nx)
 {
-    int best = 256;
+    int best = 1;
     double least = 1e300;
-    for (int cap : {256, 192, 128, 96, 64}) {
-        const int L = std::max(1, cap / nx);
+    for (int L = 256 / nx; L >= std::max(1, 64 / nx); --L) {
         const long blocks = (lines + L - 1) / L;
         const double t = (double)((blocks + 767) / 768) * (((L * nx + 15) / 16 + 3) / 4 + 0.5);
-        if (t < least) {
+        if (t <= least) {
             least = t;
-            best = cap;
+            best = L;
         }
     }
     return best;
@@ -801,7 +801,7 @@ extern "C" int cpf_batch_create(int n, const cpf_problem *const *probs, const cp
     }
     if (wave_xpass_on(s))
         for (auto &h : s->rv)
-            set_lines(h, std::max(1, wave_block_voxels((long)h.ny * h.nz, h.nx) / h.nx));
+            set_lines(h, wave_block_lines((long)h.ny * h.nz, h.nx));
     if (s->prec != CPF_PREC_FP64) law_root_tables(s);
     if (s->prec == CPF_PREC_FP64) { layout<double>(s); pass_grids<double>(s); }
     else { layout<float>(s); pass_grids<float>(s); }
@@ -1818,6 +1818,15 @@ extern "C" int cpf_solver_tiles(const cpf_solver *s, int rve, int *ty, int *tz)
 // ---------------------------------------------------------------------------
 // component operators (RVE 0)
 // ---------------------------------------------------------------------------
+// LDS of an x pass without the law: the block's lines of three complex
+// fields.  (With the law's work area as well, 106 KB in FP64, one block ran
+// per CU.)
+template <typename R>
+static size_t xline_lds_bytes(const RveHost &h)
+{
+    return 3 * (size_t)h.tpbx * sizeof(C2<R>);
+}
+
 // The component operators work on caller spectra [nz][ny][nx/2+1][6]: all
 // columns, unpadded rows.
 template <typename R>
@@ -1825,6 +1834,7 @@ static RveHost op_host(const RveHost &solve)
 {
     RveHost h = solve;
     h.nkx = h.nhp = h.nhx;
+    set_lines(h, std::max(1, 256 / h.nx));
     set_tiles<R>(h, std::min(h.ty, h.nkx), std::min(h.tz, h.nkx));
     return h;
 }
@@ -1837,7 +1847,7 @@ static int op_fft_impl(cpf_solver *s, const void *field, void *spec)
     const RveDev<R> d = make_dev<R>(s, h, 0, 0, 0);
     RveDev<R> *tab = dptr<RveDev<R>>(s, s->off_opdev);
     HIPCHK(hipMemcpyAsync(tab, &d, sizeof d, hipMemcpyHostToDevice, s->stream));
-    hipLaunchKernelGGL(k_xpass_fwd<R>, dim3(h.nbx), dim3(256), s->lds_x, s->stream, (const R *)field, sp, d);
+    hipLaunchKernelGGL(k_xpass_fwd<R>, dim3(h.nbx), dim3(256), xline_lds_bytes<R>(h), s->stream, (const R *)field, sp, d);
     launch_y<R>(s, false, tab, 1, h.nty * h.nz, lds_y_bytes<R>(h, h.ty), sp, 6 * h.ny * h.ty, y_kinds<R>(h, h.ty));
     launch_z<R>(s, ZMODE_FWD, tab, 1, h.nbz, lds_z_bytes<R>(h, h.tz), sp, 6 * h.nz * h.tz, z_kinds<R>(h, h.tz));
     HIPCHK(hipGetLastError());
@@ -1863,7 +1873,7 @@ static int op_green_impl(cpf_solver *s, void *spec, void *outp, double *err2)
     HIPCHK(hipMemcpyAsync(tab, &d, sizeof d, hipMemcpyHostToDevice, s->stream));
     launch_z<R>(s, ZMODE_GREEN, tab, 1, h.nbz, lds_z_bytes<R>(h, h.tz), sp, 6 * h.nz * h.tz, z_kinds<R>(h, h.tz));
     launch_y<R>(s, true, tab, 1, h.nty * h.nz, lds_y_bytes<R>(h, h.ty), sp, 6 * h.ny * h.ty, y_kinds<R>(h, h.ty));
-    hipLaunchKernelGGL(k_xpass_inv<R>, dim3(h.nbx), dim3(256), s->lds_x, s->stream, sp, (R *)outp, d);
+    hipLaunchKernelGGL(k_xpass_inv<R>, dim3(h.nbx), dim3(256), xline_lds_bytes<R>(h), s->stream, sp, (R *)outp, d);
     HIPCHK(hipGetLastError());
     if (err2) {
         std::vector<double> pz(h.nbz);
@@ -2044,7 +2054,7 @@ static int adjoint_equilibrium(cpf_solver *s, const cpf_path *path, int n, const
     int queued = 0, chunk = 8;
     for (;;) {
         for (int c = 0; c < chunk; ++c, ++queued) {
-            hipLaunchKernelGGL(k_adj_xpass<R>, dim3(h.nbx), dim3(256), s->lds_x, s->stream, a);
+            hipLaunchKernelGGL(k_adj_xpass<R>, dim3(h.nbx), dim3(256), xline_lds_bytes<R>(h), s->stream, a);
             launch_y<R>(s, false);
             launch_z<R>(s, ZMODE_FWD | ZMODE_GREEN);
             launch_y<R>(s, true);

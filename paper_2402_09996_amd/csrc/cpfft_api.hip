@@ -1199,8 +1199,8 @@ static void launch_xiter_any(cpf_solver *s, const LawP<R> &P)
 
 // table/nrve/grid default to the whole batch; the component operators and
 // the autotuner pass a one-RVE table and an explicit spectrum.  nbc > 0:
-// the fixed-length kernel's launch also runs the first stage of the scalar
-// reduction in nbc leading blocks (the caller then skips k_bc_partials).
+// the launch also runs the first stage of the scalar reduction in nbc
+// leading blocks.
 template <typename R>
 static void launch_y(cpf_solver *s, bool inv, const RveDev<R> *table = nullptr, int nrve = 0, int grid = 0,
                      size_t lds = 0, C2<R> *spec = nullptr, int elems = 0, int kinds = 0, int nbc = 0)
@@ -1222,23 +1222,30 @@ static void launch_y(cpf_solver *s, bool inv, const RveDev<R> *table = nullptr, 
                                spec, nbc);
     }
     if (!(kinds & 2)) return;
+    if (kinds & 1) nbc = 0;   // done above
     // registers for fewer elements per thread when the tiles allow it
     constexpr int EQ = EPT_Y / 4, EH = EPT_Y / 2;
     if (elems <= EQ * 256) {
         if (inv)
-            hipLaunchKernelGGL((k_ypass<R, true, EQ>), dim3(grid), dim3(256), lds, s->stream, table, nrve, spec);
+            hipLaunchKernelGGL((k_ypass<R, true, EQ>), dim3(grid + nbc), dim3(256), lds, s->stream, table, nrve, spec,
+                               nbc);
         else
-            hipLaunchKernelGGL((k_ypass<R, false, EQ>), dim3(grid), dim3(256), lds, s->stream, table, nrve, spec);
+            hipLaunchKernelGGL((k_ypass<R, false, EQ>), dim3(grid + nbc), dim3(256), lds, s->stream, table, nrve, spec,
+                               nbc);
     } else if (elems <= EH * 256) {
         if (inv)
-            hipLaunchKernelGGL((k_ypass<R, true, EH>), dim3(grid), dim3(256), lds, s->stream, table, nrve, spec);
+            hipLaunchKernelGGL((k_ypass<R, true, EH>), dim3(grid + nbc), dim3(256), lds, s->stream, table, nrve, spec,
+                               nbc);
         else
-            hipLaunchKernelGGL((k_ypass<R, false, EH>), dim3(grid), dim3(256), lds, s->stream, table, nrve, spec);
+            hipLaunchKernelGGL((k_ypass<R, false, EH>), dim3(grid + nbc), dim3(256), lds, s->stream, table, nrve, spec,
+                               nbc);
     } else {
         if (inv)
-            hipLaunchKernelGGL((k_ypass<R, true, EPT_Y>), dim3(grid), dim3(256), lds, s->stream, table, nrve, spec);
+            hipLaunchKernelGGL((k_ypass<R, true, EPT_Y>), dim3(grid + nbc), dim3(256), lds, s->stream, table, nrve, spec,
+                               nbc);
         else
-            hipLaunchKernelGGL((k_ypass<R, false, EPT_Y>), dim3(grid), dim3(256), lds, s->stream, table, nrve, spec);
+            hipLaunchKernelGGL((k_ypass<R, false, EPT_Y>), dim3(grid + nbc), dim3(256), lds, s->stream, table, nrve, spec,
+                               nbc);
     }
 }
 
@@ -1275,7 +1282,7 @@ static void launch_z(cpf_solver *s, int mode, const RveDev<R> *table = nullptr, 
 }
 
 template <typename R>
-static void launch_bc(cpf_solver *s, bool partials_done = false)
+static void launch_bc(cpf_solver *s)
 {
     BcArgs b;
     b.n_slip = s->n_slip;
@@ -1283,12 +1290,10 @@ static void launch_bc(cpf_solver *s, bool partials_done = false)
     b.tol = s->opt.tol;
     b.stag_tol = s->opt.stag_tol;
     b.max_iter = s->opt.max_iter;
-    // two stages: BC_CHUNKS blocks per RVE sum fixed chunks of the block
-    // partials (a 128^3 x pass leaves 8192 x 11 doubles), one wave per RVE
-    // sums the chunks and updates the scalars
-    if (!partials_done)
-        hipLaunchKernelGGL(k_bc_partials<R>, dim3(s->rv.size() * BC_CHUNKS), dim3(256), 0, s->stream,
-                           dptr<RveDev<R>>(s, s->off_dev));
+    // second of two stages: BC_CHUNKS blocks per RVE of the inverse y pass's
+    // launch sum fixed chunks of the block partials (a 128^3 x pass leaves
+    // 8192 x 11 doubles), one wave per RVE sums the chunks and updates the
+    // scalars
     hipLaunchKernelGGL(k_bc_update<R>, dim3(s->rv.size()), dim3(64), 0, s->stream,
                        dptr<RveDev<R>>(s, s->off_dev), b);
 }
@@ -1308,12 +1313,11 @@ static int launch_iteration(cpf_solver *s, const LawP<R> &P)
     { TraceRange t("cpf x pass (law, x transforms)"); TIMED(s, 0, launch_xiter_any<R>(s, P)); }
     { TraceRange t("cpf y pass"); TIMED(s, 1, launch_y<R>(s, false)); }
     { TraceRange t("cpf z pass (Green operator)"); TIMED(s, 2, launch_z<R>(s, ZMODE_FWD | ZMODE_GREEN)); }
-    // the first stage of the scalar reduction rides in the inverse y pass's
-    // launch when the fixed-length kernel runs it (one launch less per
+    // with the first stage of the scalar reduction (one launch less per
     // iteration)
-    const int nbc = (s->y_kinds & 1) ? (int)s->rv.size() * BC_CHUNKS : 0;
+    const int nbc = (int)s->rv.size() * BC_CHUNKS;
     { TraceRange t("cpf y pass (inverse)"); TIMED(s, 3, launch_y<R>(s, true, nullptr, 0, 0, 0, nullptr, 0, 0, nbc)); }
-    { TraceRange t("cpf boundary update"); TIMED(s, 4, launch_bc<R>(s, nbc > 0)); }
+    { TraceRange t("cpf boundary update"); TIMED(s, 4, launch_bc<R>(s)); }
     return CPF_OK;
 }
 

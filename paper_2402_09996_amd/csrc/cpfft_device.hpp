@@ -395,6 +395,7 @@ __device__ void strided_fft(C2<R> *buf, int es, int nl, const FftPlan &P, const 
 // written to global memory.
 // ---------------------------------------------------------------------------
 template <int N> struct FixedPlan { static constexpr int np = 0, r0 = 1, r1 = 1, r2 = 1; };
+template <> struct FixedPlan<16> { static constexpr int np = 2, r0 = 4, r1 = 4, r2 = 1; };
 template <> struct FixedPlan<32> { static constexpr int np = 2, r0 = 8, r1 = 4, r2 = 1; };
 template <> struct FixedPlan<48> { static constexpr int np = 2, r0 = 16, r1 = 3, r2 = 1; };
 template <> struct FixedPlan<64> { static constexpr int np = 2, r0 = 8, r1 = 8, r2 = 1; };

@@ -725,6 +725,33 @@ __global__ __launch_bounds__(256) void k_xpass_inv(const C2<R> *__restrict__ spe
 }
 
 // ---------------------------------------------------------------------------
+// First stage of the scalar reduction: BC_CHUNKS blocks per RVE each sum a
+// fixed contiguous chunk of the x-pass block sums (NPX values each) and of
+// the z-pass residual sums, in a fixed order; b = RVE * BC_CHUNKS + chunk.
+// 256 threads.
+// ---------------------------------------------------------------------------
+constexpr int BC_CHUNKS = 32;
+
+template <typename R>
+__device__ __forceinline__ void bc_partials_block(const RveDev<R> *__restrict__ rv, int b)
+{
+    const RveDev<R> &d = rv[b / BC_CHUNKS];
+    const int c = b % BC_CHUNKS;
+    if (d.sc->done) return;
+    const int nbx = (d.nlines + d.L - 1) / d.L, nbz = d.ntz * d.ny;
+    const int x0 = (int)((long)nbx * c / BC_CHUNKS), x1 = (int)((long)nbx * (c + 1) / BC_CHUNKS);
+    const int z0 = (int)((long)nbz * c / BC_CHUNKS), z1 = (int)((long)nbz * (c + 1) / BC_CHUNKS);
+    double acc[NPX + 1];
+#pragma unroll
+    for (int i = 0; i < NPX + 1; ++i) acc[i] = 0.0;
+    for (int j = x0 + threadIdx.x; j < x1; j += blockDim.x)
+#pragma unroll
+        for (int i = 0; i < NPX; ++i) acc[i] += d.part_x[(long)j * NPX + i];
+    for (int j = z0 + threadIdx.x; j < z1; j += blockDim.x) acc[NPX] += d.part_z[j];
+    block_sum<NPX + 1, 4>(acc, d.part_b + (long)c * (NPX + 1));
+}
+
+// ---------------------------------------------------------------------------
 // y pass: C2C along y on the half spectrum, stored [z][y][kx][c] (the six
 // components of a frequency adjacent).  Block = one z, a tile of ty
 // consecutive kx columns: 6 ty lines (column-major, components adjacent),
@@ -733,12 +760,20 @@ __global__ __launch_bounds__(256) void k_xpass_inv(const C2<R> *__restrict__ spe
 // outputs straight back; the middle passes run in LDS laid out [y][line].
 // ---------------------------------------------------------------------------
 // spec_override (component operators): transform this array instead of the
-// RVE's own spectrum, and ignore the step flag.
+// RVE's own spectrum, and ignore the step flag.  nbc > 0 (a multiple of 8,
+// so that the XCD of each transform block is unchanged): the first nbc
+// blocks of the launch are the first stage of the scalar reduction instead
+// of a launch of their own (4 of the 145 us of a 36^3 iteration); the x and
+// z passes that wrote its inputs ran before.
 template <typename R, bool INV, int EPT>
 __global__ __launch_bounds__(256) void k_ypass(const RveDev<R> *__restrict__ rv, int nrve,
-                                               C2<R> *spec_override)
+                                               C2<R> *spec_override, int nbc)
 {
-    const int blk = xcd_block((int)blockIdx.x, (int)gridDim.x);
+    if ((int)blockIdx.x < nbc) {
+        bc_partials_block<R>(rv, (int)blockIdx.x);
+        return;
+    }
+    const int blk = xcd_block((int)blockIdx.x - nbc, (int)gridDim.x - nbc);
     const int r = find_rve(rv, nrve, blk, 1);
     const RveDev<R> &d = rv[r];
     if ((!spec_override && d.sc->done) || d.yfix) return;
@@ -964,33 +999,6 @@ __global__ __launch_bounds__(Z_THREADS) void k_zpass_green(const RveDev<R> *__re
 }
 
 // ---------------------------------------------------------------------------
-// First stage of the scalar reduction: BC_CHUNKS blocks per RVE each sum a
-// fixed contiguous chunk of the x-pass block sums (NPX values each) and of
-// the z-pass residual sums, in a fixed order; b = RVE * BC_CHUNKS + chunk.
-// 256 threads.
-// ---------------------------------------------------------------------------
-constexpr int BC_CHUNKS = 32;
-
-template <typename R>
-__device__ __forceinline__ void bc_partials_block(const RveDev<R> *__restrict__ rv, int b)
-{
-    const RveDev<R> &d = rv[b / BC_CHUNKS];
-    const int c = b % BC_CHUNKS;
-    if (d.sc->done) return;
-    const int nbx = (d.nlines + d.L - 1) / d.L, nbz = d.ntz * d.ny;
-    const int x0 = (int)((long)nbx * c / BC_CHUNKS), x1 = (int)((long)nbx * (c + 1) / BC_CHUNKS);
-    const int z0 = (int)((long)nbz * c / BC_CHUNKS), z1 = (int)((long)nbz * (c + 1) / BC_CHUNKS);
-    double acc[NPX + 1];
-#pragma unroll
-    for (int i = 0; i < NPX + 1; ++i) acc[i] = 0.0;
-    for (int j = x0 + threadIdx.x; j < x1; j += blockDim.x)
-#pragma unroll
-        for (int i = 0; i < NPX; ++i) acc[i] += d.part_x[(long)j * NPX + i];
-    for (int j = z0 + threadIdx.x; j < z1; j += blockDim.x) acc[NPX] += d.part_z[j];
-    block_sum<NPX + 1, 4>(acc, d.part_b + (long)c * (NPX + 1));
-}
-
-// ---------------------------------------------------------------------------
 // Fixed-length y and z passes: the common lengths (fixed_len) with their
 // radix plans and the tile width known at compile time (fixed_tile columns
 // of 6 components), 256 threads.  The same transforms as k_ypass and
@@ -1000,7 +1008,7 @@ constexpr int FX_THREADS = 256;   // threads of the fixed-length y and z blocks
 
 __host__ __device__ constexpr bool fixed_len(int n)
 {
-    return n == 32 || n == 48 || n == 64 || n == 96 || n == 128 || n == 256;
+    return n == 16 || n == 32 || n == 48 || n == 64 || n == 96 || n == 128 || n == 256;
 }
 template <typename R, int N>
 __host__ __device__ constexpr int fixed_tile()
@@ -1026,10 +1034,7 @@ __device__ __forceinline__ void ypass_fixed(const RveDev<R> &d, C2<R> *g, C2<R> 
     fixed_fft<R, INV, N, NL, FX_THREADS, true, true>(buf, nlv, twl, gline, 6L * d.nhp, stage);
 }
 
-// nbc > 0 (a multiple of 8, so that the XCD of each transform block is
-// unchanged): the first nbc blocks of the launch are the first stage of the
-// scalar reduction (bc_partials_block) instead of a launch of their own;
-// the x and z passes that wrote its inputs ran before.
+// nbc: as for k_ypass.
 template <typename R, bool INV>
 __global__ __launch_bounds__(FX_THREADS) void k_ypass_fx(const RveDev<R> *__restrict__ rv, int nrve, C2<R> *spec_override,
                                                   int nbc)
@@ -1050,6 +1055,7 @@ __global__ __launch_bounds__(FX_THREADS) void k_ypass_fx(const RveDev<R> *__rest
     const int nlv = 6 * min(d.ty, d.nkx - kx0);
     C2<R> *g = (spec_override ? spec_override : d.spec) + ((long)z * d.ny * d.nhp + kx0) * 6;
     switch (d.ny) {
+    case 16: ypass_fixed<R, INV, 16>(d, g, buf, nlv); break;
     case 32: ypass_fixed<R, INV, 32>(d, g, buf, nlv); break;
     case 48: ypass_fixed<R, INV, 48>(d, g, buf, nlv); break;
     case 64: ypass_fixed<R, INV, 64>(d, g, buf, nlv); break;
@@ -1122,6 +1128,7 @@ __global__ __launch_bounds__(FX_THREADS) void k_zpass_fx(const RveDev<R> *__rest
     const int tw_ = min(d.tz, d.nkx - kx0);
     C2<R> *spec = (spec_override ? spec_override : d.spec) + ((long)ky * d.nhp + kx0) * 6;
     switch (d.nz) {
+    case 16: zpass_fixed<R, 16>(d, spec, buf, tw_, kx0, ky, local, inv_mu0, coef, mode); break;
     case 32: zpass_fixed<R, 32>(d, spec, buf, tw_, kx0, ky, local, inv_mu0, coef, mode); break;
     case 48: zpass_fixed<R, 48>(d, spec, buf, tw_, kx0, ky, local, inv_mu0, coef, mode); break;
     case 64: zpass_fixed<R, 64>(d, spec, buf, tw_, kx0, ky, local, inv_mu0, coef, mode); break;
@@ -1436,15 +1443,6 @@ __global__ __launch_bounds__(256) void k_aa_update(const RveDev<R> *__restrict__
     }
 #pragma unroll
     for (int c = 0; c < 6; ++c) eps_k[c * d.nvox + vox] = e[c];
-}
-
-// First stage of the scalar reduction as its own launch (the iteration runs
-// it inside the inverse y pass's launch where that pass is the fixed-length
-// kernel).
-template <typename R>
-__global__ __launch_bounds__(256) void k_bc_partials(const RveDev<R> *__restrict__ rv)
-{
-    bc_partials_block<R>(rv, (int)blockIdx.x);
 }
 
 // One block per RVE: sum the chunk sums (fixed order), evaluate the

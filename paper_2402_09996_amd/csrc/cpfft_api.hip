@@ -664,7 +664,7 @@ static bool wave_xpass_on(const cpf_solver *s)
 }
 
 // The tables of root_solve (FP32): G = min(X, X/n) - Y with the root Y of
-// log2(2^Y + 2^(nY)) = X by bisection, and log2 of the crossover overstress
+// log2(2^Y + 2^(nY)) = X by Newton's method, and log2 of the crossover overstress
 // o* = (K^n / eta)^(1/(n-1)).  Close to n = 1, where the crossover moves
 // away, the families go without.
 static void law_root_tables(cpf_solver *s)
@@ -678,12 +678,13 @@ static void law_root_tables(cpf_solver *s)
         for (int i = 0; i < LAW_ROOT_WORDS; ++i) {
             const int k = i - LAW_ROOT_MID;
             const double X = k > 0 ? 0.25 * k : 0.5 * k / (L.n - 1.0), m = X < X / L.n ? X : X / L.n;
-            double a = m - 1.0, b = m;
-            for (int it = 0; it < 40; ++it) {
-                const double Y = 0.5 * (a + b);
-                (log2(exp2(Y) + exp2(L.n * Y)) > X ? b : a) = Y;
+            double Y = m;   // above the root of a convex function: Newton descends to it
+            for (int it = 0; it < 30; ++it) {
+                const double u = exp2(Y), v = exp2(L.n * Y), step = (log2(u + v) - X) * (u + v) / (u + L.n * v);
+                Y -= step;
+                if (step < 1e-12) break;
             }
-            s->root[f][i] = m - 0.5 * (a + b);
+            s->root[f][i] = m - Y;
         }
     }
 }
@@ -2273,6 +2274,25 @@ extern "C" int cpf_adjoint_vjp(cpf_solver *s, const cpf_path *path, const double
 // ---------------------------------------------------------------------------
 // von Mises stress histogram of the committed state
 // ---------------------------------------------------------------------------
+// 16 bytes per lane and component where every component's row is aligned to
+// them, else one voxel.
+template <typename R>
+static void launch_hist(const R *sig, long nvox, int nbins, double lo, double w, const double *q,
+                        unsigned long long *counts, hipStream_t st)
+{
+    constexpr int VEC = 16 / sizeof(R);
+    const bool vec = nvox % VEC == 0 && reinterpret_cast<uintptr_t>(sig) % 16 == 0;
+    const long packs = vec ? nvox / VEC : nvox;
+    const dim3 grid(std::min<long>((packs + 255) / 256, 2048));
+    const size_t lds = sizeof(double) * (nbins + 1) + sizeof(unsigned int) * (nbins + 2);
+    if (vec)
+        hipLaunchKernelGGL((k_seq_hist<R, VEC>), grid, dim3(256), lds, st, sig, nvox, nbins, float(lo), float(1.0 / w),
+                           q, counts);
+    else
+        hipLaunchKernelGGL((k_seq_hist<R, 1>), grid, dim3(256), lds, st, sig, nvox, nbins, float(lo), float(1.0 / w),
+                           q, counts);
+}
+
 template <typename R>
 static int seq_hist_impl(cpf_solver *s, int rve, int nbins, double lo, double hi, unsigned long long *counts)
 {
@@ -2298,10 +2318,7 @@ static int seq_hist_impl(cpf_solver *s, int rve, int nbins, double lo, double hi
         hipLaunchKernelGGL(k_stress_field<R>, dim3((h.nvox + 255) / 256), dim3(256), 0, s->stream,
                            dptr<int32_t>(s, h.off_labels), dptr<R>(s, h.off_Q), dptr<R>(s, h.off_eps[h.cur]),
                            dptr<R>(s, h.off_st[h.cur]), sig, P, h.nvox);
-        const long blocks = std::min<long>((h.nvox + 255) / 256, 2048);
-        const size_t lds = sizeof(double) * (nbins + 1) + sizeof(unsigned int) * (nbins + 2);
-        hipLaunchKernelGGL(k_seq_hist<R>, dim3(blocks), dim3(256), lds, s->stream, (const R *)sig, h.nvox, nbins,
-                           (const double *)dq, dc);
+        launch_hist<R>(sig, h.nvox, nbins, lo, w, dq, dc, s->stream);
         HIPCHK(hipGetLastError());
     }
     HIPCHK(hipMemcpyAsync(counts, dc, sizeof(unsigned long long) * (nbins + 2), hipMemcpyDeviceToHost, s->stream));
@@ -2390,16 +2407,11 @@ extern "C" int cpf_seq_histogram_field(const void *dev_sig, int precision, long 
     // the array keeps the previous call's counts: clear them (a kernel, no memset node)
     hipLaunchKernelGGL(k_fill<unsigned long long>, dim3(16), dim3(256), 0, st, dc, (long)nbins + 2, 0ull);
     hipLaunchKernelGGL(k_hist_edges, dim3((nbins + 256) / 256), dim3(256), 0, st, lo, (hi - lo) / nbins, nbins, dq);
-    if (nvox > 0) {
-        const long blocks = std::min<long>((nvox + 255) / 256, 2048);
-        const size_t lds = sizeof(double) * (nbins + 1) + sizeof(unsigned int) * (nbins + 2);
-        if (precision == CPF_PREC_FP64)
-            hipLaunchKernelGGL(k_seq_hist<double>, dim3(blocks), dim3(256), lds, st, (const double *)dev_sig,
-                               (long)nvox, nbins, (const double *)dq, dc);
-        else
-            hipLaunchKernelGGL(k_seq_hist<float>, dim3(blocks), dim3(256), lds, st, (const float *)dev_sig,
-                               (long)nvox, nbins, (const double *)dq, dc);
-    }
+    const double w = (hi - lo) / nbins;
+    if (nvox > 0 && precision == CPF_PREC_FP64)
+        launch_hist<double>((const double *)dev_sig, (long)nvox, nbins, lo, w, dq, dc, st);
+    else if (nvox > 0)
+        launch_hist<float>((const float *)dev_sig, (long)nvox, nbins, lo, w, dq, dc, st);
     HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(counts, dc, sizeof(unsigned long long) * (nbins + 2), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));

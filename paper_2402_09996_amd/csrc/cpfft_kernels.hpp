@@ -1678,35 +1678,53 @@ __device__ __forceinline__ double von_mises_sq_exact(const R s[6])
 // rounded on the device) out of the decision.  Block-local counts in LDS,
 // added to the device counts at the end (integer atomics: the result does
 // not depend on the order).
-template <typename R>
-__global__ __launch_bounds__(256) void k_seq_hist(const R *__restrict__ sig, long nvox, int nbins,
+//
+// The field is read once, past the caches, VEC adjacent voxels per lane in
+// one load per component: more bytes in flight, and the voxels' chains
+// overlap.  The bin is guessed from the FP32 root (the edges are equidistant
+// from lo, iw = 1 / width) and checked against both of its edges; only where
+// the guess fails, a binary search of the edges.  FP32 at 256^3 (402 MB) and
+// 150 bins: 85 us, 4.75 TB/s; one voxel per lane and a binary search for
+// each 115.
+template <typename R, int VEC>
+__global__ __launch_bounds__(256) void k_seq_hist(const R *__restrict__ sig, long nvox, int nbins, float lo, float iw,
                                                   const double *__restrict__ qedge, unsigned long long *counts)
 {
+    typedef R Pack __attribute__((ext_vector_type(VEC)));
     extern __shared__ double lds_q[];
     unsigned int *hist = reinterpret_cast<unsigned int *>(lds_q + nbins + 1);
     const int nb = nbins + 2;
     for (int i = threadIdx.x; i <= nbins; i += blockDim.x) lds_q[i] = qedge[i];
     for (int i = threadIdx.x; i < nb; i += blockDim.x) hist[i] = 0u;
     __syncthreads();
-    for (long vox = (long)blockIdx.x * blockDim.x + threadIdx.x; vox < nvox; vox += (long)gridDim.x * blockDim.x) {
-        R sl[6];
+    for (long p = (long)blockIdx.x * blockDim.x + threadIdx.x; p < nvox / VEC; p += (long)gridDim.x * blockDim.x) {
+        Pack f[6];
 #pragma unroll
-        for (int c = 0; c < 6; ++c) sl[c] = sig[c * nvox + vox];
-        const double x = von_mises_sq_exact<R>(sl);
-        int k;
-        if (!(x == x) || x == INFINITY) {
-            k = nbins + 1;
-        } else {
-            // largest j with lds_q[j] <= x, -1 if none
-            int a = -1, b = nbins;
-            while (a < b) {
-                const int mid = (a + b + 1) >> 1;
-                if (lds_q[mid] <= x) a = mid;
-                else b = mid - 1;
+        for (int c = 0; c < 6; ++c) f[c] = __builtin_nontemporal_load(reinterpret_cast<const Pack *>(sig + c * nvox + p * VEC));
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) {
+            R sl[6];
+#pragma unroll
+            for (int c = 0; c < 6; ++c) sl[c] = f[c][q];
+            const double x = von_mises_sq_exact<R>(sl);
+            int k = nbins + 1;
+            if (x < INFINITY) {
+                // largest j with lds_q[j] <= x, -1 if none
+                const float t = (__builtin_amdgcn_sqrtf((float)x) - lo) * iw;
+                int a = (int)fminf(fmaxf(t, 0.f), (float)(nbins - 1));
+                if (!(lds_q[a] <= x && x < lds_q[a + 1])) {
+                    int b = nbins;
+                    a = -1;
+                    while (a < b) {
+                        const int mid = (a + b + 1) >> 1;
+                        if (lds_q[mid] <= x) a = mid;
+                        else b = mid - 1;
+                    }
+                }
+                k = a + 1;
             }
-            k = a + 1;
+            atomicAdd(&hist[k], 1u);
         }
-        atomicAdd(&hist[k], 1u);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < nb; i += blockDim.x)

@@ -516,6 +516,32 @@ static void pass_grids(cpf_solver *s)
     }
 }
 
+// Lines per block of the cooperative law.  A block's four waves take its
+// groups of 16 voxels in turn, so its time goes by the groups of one wave,
+// plus about half a group for the transforms and rotations; about 768 blocks
+// are resident (three per CU).  Small problems gain from few voxels per block
+// (every CU has one; fewer than 64 leave waves without a group), large ones
+// from many, and lines that are no multiple of 64 leave waves idle; the count
+// with the least time is taken (FP64 x pass, 256 voxels and the chosen: 24^3
+// 77 / 58 us, 32^3 91 / 63, 64^3 373 / 350), of equal ones the smallest,
+// which spreads best over the CUs (48^3: 4 lines 190, 3 lines 170 us).  By
+// the member's own grid alone, so that it is computed the same in every
+// batch.
+static int wave_block_lines(long lines, int nx)
+{
+    int best = 1;
+    double least = 1e300;
+    for (int L = 256 / nx; L >= std::max(1, 64 / nx); --L) {
+        const long blocks = (lines + L - 1) / L;
+        const double t = (double)((blocks + 767) / 768) * (((L * nx + 15) / 16 + 3) / 4 + 0.5);
+        if (t <= least) {
+            least = t;
+            best = L;
+        }
+    }
+    return best;
+}
+
 template <typename R>
 static void layout(cpf_solver *s)
 {
@@ -533,7 +559,10 @@ static void layout(cpf_solver *s)
         h.off_tw[0] = take(cb * h.nx);
         h.off_tw[1] = take(cb * h.ny);
         h.off_tw[2] = take(cb * h.nz);
-        h.off_px = take(sizeof(double) * NPX * h.nbx);
+        // FP64: the block sums of either x pass, so that the options do not
+        // change the size
+        const int lines = h.ny * h.nz, Lw = sizeof(R) == 8 ? wave_block_lines(lines, h.nx) : h.L;
+        h.off_px = take(sizeof(double) * NPX * ((lines + Lw - 1) / Lw));
         h.off_pz = take(sizeof(double) * h.nhx * h.ny);   // room for the smallest z tile
         h.off_sc = take(sizeof(Scalars));
         h.off_mv = take(sizeof(int32_t) * h.nvox);
@@ -687,32 +716,6 @@ static void law_root_tables(cpf_solver *s)
             s->root[f][i] = m - Y;
         }
     }
-}
-
-// Lines per block of the cooperative law.  A block's four waves take its
-// groups of 16 voxels in turn, so its time goes by the groups of one wave,
-// plus about half a group for the transforms and rotations; about 768 blocks
-// are resident (three per CU).  Small problems gain from few voxels per block
-// (every CU has one; fewer than 64 leave waves without a group), large ones
-// from many, and lines that are no multiple of 64 leave waves idle; the count
-// with the least time is taken (FP64 x pass, 256 voxels and the chosen: 24^3
-// 77 / 58 us, 32^3 91 / 63, 64^3 373 / 350), of equal ones the smallest,
-// which spreads best over the CUs (48^3: 4 lines 190, 3 lines 170 us).  By
-// the member's own grid alone, so that it is computed the same in every
-// batch.
-static int wave_block_lines(long lines, int nx)
-{
-    int best = 1;
-    double least = 1e300;
-    for (int L = 256 / nx; L >= std::max(1, 64 / nx); --L) {
-        const long blocks = (lines + L - 1) / L;
-        const double t = (double)((blocks + 767) / 768) * (((L * nx + 15) / 16 + 3) / 4 + 0.5);
-        if (t <= least) {
-            least = t;
-            best = L;
-        }
-    }
-    return best;
 }
 
 // Members of a batch share the crystal stiffness, the systems and the law.

@@ -16,10 +16,10 @@
 // Parameter order per family (slip, twin): r0, Q, b, c, d, K, n.
 //
 // The forward integration of the step is replayed once per step by
-// k_law_record with the solver's own stage code (same specialization, same
-// Newton warm starts), so the recorded stage states and Newton roots are
-// those of the converged forward step; the reverse sweeps read them and
-// never solve for a root.
+// k_law_record with the lane law's stage code (same specialization), so the
+// recorded stage states and roots are those of the converged forward step
+// (to rounding where the forward step ran the four-lane law); the reverse
+// sweeps read them and never solve for a root.
 #pragma once
 #include "cpfft_kernels.hpp"
 

@@ -683,9 +683,10 @@ static void set_lines(RveHost &h, int L)
 // The wave-cooperative x pass: FP64, Table 1 systems, fixed substeps, the
 // implicit regularization; the rest keeps a lane per voxel.  FP32 does too
 // (cpfft_wavelaw.hpp): below 32768 voxels, where CUs are idle, the
-// cooperative law would be faster there as well (16^3 64 / 38 us, 32^3 65 /
-// 44), but a member of a batch has to be computed as in a solve of its own,
-// and in a batch that fills the chip it is slower (48^3 79 / 122).
+// cooperative law was faster there as well (16^3 64 / 38 us, 32^3 65 / 44,
+// before the tables of root_solve), but a member of a batch has to be
+// computed as in a solve of its own, and in a batch that fills the chip it
+// is slower (48^3 79 / 122).
 static bool wave_xpass_on(const cpf_solver *s)
 {
     return s->law_spec == LAW_TABLE1 && s->prec == CPF_PREC_FP64 && !(s->opt.rk_tol > 0.0) &&

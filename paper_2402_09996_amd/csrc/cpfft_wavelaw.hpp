@@ -19,10 +19,11 @@
 // FP64 matrix and vector instructions share the SIMD's FP64 units: measured
 // together they take the sum of their times, so the matrix form saves the
 // exchange between lanes, not arithmetic).  128^3, 16 systems, 4 substeps,
-// per launch over four load steps: 3882 us before, 2175 now; 64^3 847 / 590,
-// 16^3 (12 systems, 10-16 substeps) 226 / 77.  FP32 keeps a lane per voxel:
-// its three blocks per CU are bound by their instruction count, and the
-// matrix instructions here add to that (128^3: 822 us against 1169).
+// per launch over four load steps: 3882 us before, 2195 now; 64^3 847 / 600,
+// 16^3 (12 systems, 10-16 substeps) 226 / 79.  FP32 keeps a lane per voxel:
+// three of its blocks run per CU as it is, and the exchange between lanes
+// here adds instructions (128^3: 822 us with its Newton solves of that time,
+// against 1169).
 #pragma once
 #include "cpfft_device.hpp"
 

@@ -174,15 +174,17 @@ __device__ __forceinline__ double wl_sum4(double x)
     return x + __shfl_xor(x, 32, 64);
 }
 
-// E[k] exp(-x[k]) for x >= 0 into e, where the lanes of the wave mostly have
-// x <= 1/64: Taylor sums, remainder x^7 / 5040 < 5e-17.  With larger x in
-// some lane, by 18 terms up to x = 1, and beyond by halving x and squaring.
+// E[k] exp(-x[k]) into e, where the lanes of the wave mostly have |x| <= 1/64:
+// Taylor sums, remainder |x|^7 / 5040 < 5e-17.  With larger |x| in some lane
+// (of either sign: a law may have b < 0), by 18 terms up to |x| = 1, and
+// beyond by halving x and squaring; past |x| = 1100 the factor is 0 or
+// infinite.
 template <int NSL>
 __device__ __forceinline__ void wl_decay(const double (&E)[NSL], const double (&x)[NSL], double (&e)[NSL])
 {
     double xm = 0.0;
 #pragma unroll
-    for (int k = 0; k < NSL; ++k) xm = fmax(xm, x[k]);
+    for (int k = 0; k < NSL; ++k) xm = fmax(xm, fabs(x[k]));
     if (!__any(xm > 1.0 / 64.0)) {
 #pragma unroll
         for (int k = 0; k < NSL; ++k) {
@@ -196,7 +198,8 @@ __device__ __forceinline__ void wl_decay(const double (&E)[NSL], const double (&
         return;
     }
     int m = 0;
-    while (__any(xm > 1.0) && m < 64) {
+    xm = fmin(xm, 1100.0);
+    while (__any(xm > 1.0)) {
         xm *= 0.5;
         ++m;
     }
@@ -208,6 +211,8 @@ __device__ __forceinline__ void wl_decay(const double (&E)[NSL], const double (&
 #pragma unroll 1
         for (int i = 18; i > 0; --i) p = 1.0 - z * p / (double)i;
         for (int i = 0; i < m; ++i) p *= p;
+        if (x[k] > 1100.0) p = 0.0;
+        if (x[k] < -1100.0) p = INFINITY;
         e[k] = E[k] * p;
     }
 }

@@ -1,0 +1,61 @@
+"""Single crystals under prescribed strain against the oracle, at law
+parameters and strains off the ordinary range.  Every voxel has the mean
+strain then, so that the results are those of the law alone."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+import rvegen
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+cp = pytest.importorskip("paper_2402_09996_amd")
+
+DIRECTION = np.array([1.0, -0.45, -0.55, 0.12, -0.2, 0.31])
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    cp._lib.lib()
+    yield
+
+
+def _relerr(a, b):
+    a, b = np.asarray(a, float), np.asarray(b, float)
+    return float(np.linalg.norm(a - b) / max(np.linalg.norm(b), 1e-300))
+
+
+def _crystal(strains, dt, shape=(2, 2, 4), systems=None, eta=None, **family):
+    """Workload of one crystal (no twins) along multiples of DIRECTION."""
+    C, law = rvegen.config_law()
+    law.slip = dataclasses.replace(law.slip, **family)
+    if eta is not None:
+        law.eta = eta
+    path = rvegen.LoadPath(t=np.arange(len(strains) + 1) * dt, strain_ctrl=np.ones((len(strains), 6), np.uint8),
+                           target=np.outer(strains, DIRECTION))
+    return rvegen.Workload("crystal", rvegen.make_rve(shape, 1, 5), systems or rvegen.config_systems(False), C, law,
+                           path)
+
+
+def _both(w, M, precision="fp64"):
+    s = cp.Solver(cp.Problem.from_workload(w), precision=precision, tol=1e-11, rk4_M=M)
+    R = s.run(w.path)
+    ref = oracle.solver_for(w, oracle.Options(tol=1e-11, M=M)).run(w.path, keep_fields=True)
+    return s, R, ref
+
+
+# b v below and above the bounds of the series of the saturation term, with
+# the sign of accelerating hardening; ordinary b beside them.  Sums of some
+# hundred rounded terms: 1e-12.
+@pytest.mark.parametrize("b,M", [(10.0, 1), (-10.0, 1), (-300.0, 8), (-1000.0, 1), (-3000.0, 8), (-10000.0, 1)])
+def test_hardening_of_either_sign_matches_oracle(b, M):
+    print("case", b, M, flush=True)
+    w = _crystal([1e-3, 2e-3, 3e-3], 0.4, b=b, Q=400.0 / b, c=0.0, d=0.0)
+    s, R, ref = _both(w, M)
+    assert ref.mean_v[-1] > 1e-4
+    assert _relerr(R["Sigma"], ref.Sigma) < 1e-12
+    assert _relerr(s.field("acc_slip").cpu().numpy(), ref.fields["acc_slip"]) < 1e-12

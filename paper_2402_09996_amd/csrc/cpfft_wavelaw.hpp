@@ -255,8 +255,11 @@ __device__ __forceinline__ void wave_law(const LawP<double> &P, const double *ta
         const double *rc = rows + col, *pc = tab + WL_PC * 64 + lane;
 #pragma unroll
         for (int k = 0; k < NSL; ++k) {
+            // a column without a voxel has the back strain NaN: no system of
+            // it is active then, with a negative initial resistance neither,
+            // and it adds nothing to the sums
             v[k] = in ? st_in[(6 + wl_sys(g, k)) * N + vox] : 0.0;
-            al[k] = in ? st_in[(6 + S + wl_sys(g, k)) * N + vox] : 0.0;
+            al[k] = in ? st_in[(6 + S + wl_sys(g, k)) * N + vox] : __builtin_nan("");
             E[k] = ex2(-(k < 3 ? P.fs.bl2e : P.ft.bl2e) * v[k]);
             y[k] = gp[k] = 0.0;
         }

@@ -59,3 +59,19 @@ def test_hardening_of_either_sign_matches_oracle(b, M):
     assert ref.mean_v[-1] > 1e-4
     assert _relerr(R["Sigma"], ref.Sigma) < 1e-12
     assert _relerr(s.field("acc_slip").cpu().numpy(), ref.fields["acc_slip"]) < 1e-12
+
+
+# Groups of 16 voxels that are full and partly empty; negative initial
+# resistances, with which a system slips at zero stress.  The sums over the
+# grid are one crystal's values, whatever its size.
+def test_sums_leave_out_voxels_that_are_not_there():
+    S = rvegen.config_systems(False)
+    S = dataclasses.replace(S, tau0=np.full_like(S.tau0, -5.0))
+    per_voxel = []
+    for shape in ((2, 2, 4), (2, 2, 3), (3, 3, 3)):
+        print("case", shape, flush=True)
+        s, R, ref = _both(_crystal([1e-4, 2e-4], 0.1, shape, systems=S, c=0.0, d=0.0), 4)
+        assert _relerr(R["mean_v"], ref.mean_v) < 1e-11
+        assert np.array_equal(R["iters"], ref.iters)
+        per_voxel.append(R["n_active"] / np.prod(shape))
+    assert all(np.array_equal(p, per_voxel[0]) for p in per_voxel)

@@ -149,10 +149,12 @@ __device__ __forceinline__ double wl_newton(double o, double A, double y, double
         if (!(z < yk)) z = yk;
         if (__any(cold)) {
             asm volatile("");
-            // an upper bound is enough: FP32, raised by 1e-5 (newton_solve)
+            // an upper bound is enough: FP32, raised by 1e-5 (newton_solve);
+            // where it underflows o/K is taken, since the logarithm of a
+            // start at 0 would be infinite (0^0 for n = 1: NaN)
             const float w = (float)o * __builtin_amdgcn_rcpf((float)etaA);
             const double yc = (double)ex2(lg2(w) * __builtin_amdgcn_rcpf((float)n)) * (1.0 + 1e-5);
-            if (cold) z = yk < yc ? yk : yc;
+            if (cold) z = yk < yc || !(yc > 0.0) ? yk : yc;
         }
     }
 #pragma unroll 1

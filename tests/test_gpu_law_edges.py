@@ -75,3 +75,17 @@ def test_sums_leave_out_voxels_that_are_not_there():
         assert np.array_equal(R["iters"], ref.iters)
         per_voxel.append(R["n_active"] / np.prod(shape))
     assert all(np.array_equal(p, per_voxel[0]) for p in per_voxel)
+
+
+# Overstresses below the range of the FP32 start of the FP64 roots, without
+# initial resistance.  The law is linear there (n = 1: o = (K + eta) y, the
+# hardening below rounding); some hundred rounded terms: 1e-12.
+@pytest.mark.parametrize("strain", [1e-35, 1e-40, 1e-44])
+def test_linear_law_at_vanishing_overstress_matches_oracle(strain):
+    print("case", strain, flush=True)
+    w = _crystal([strain, 2 * strain, 3 * strain], 1.0, systems=rvegen.config_systems(False, 0.0, 0.0), n=1.0,
+                 K=2000.0, c=0.0, d=0.0)
+    s, R, ref = _both(w, 4)
+    assert ref.mean_v[-1] > 0.0
+    assert _relerr(R["Sigma"], ref.Sigma) < 1e-12
+    assert _relerr(s.field("acc_slip").cpu().numpy(), ref.fields["acc_slip"]) < 1e-12

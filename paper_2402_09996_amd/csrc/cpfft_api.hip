@@ -953,6 +953,7 @@ static LawP<R> make_law(const cpf_solver *s)
         F.n = R(L.n); F.inv_n = R(1.0 / L.n); F.nm1 = R(L.n - 1.0);
         F.nm1_int = (L.n == floor(L.n) && L.n >= 1.0 && L.n <= 64.0) ? (int)L.n - 1 : -1;
         F.Q = R(L.Q); F.b = R(L.b); F.qs = R(L.q_self); F.ql = R(L.q_latent);
+        F.u_max = R(std::min(0.06, 0.6 / L.n));
         if (sizeof(R) == 4) {
             F.lo = R(s->root_lo[f]); F.lok = R(s->root_lo[f] - log2(L.K)); F.inv_nm1 = R(1.0 / (L.n - 1.0));
             for (int i = 0; i < LAW_ROOT_WORDS; ++i) P.root[f * LAW_ROOT_WORDS + i] = R(s->root[f][i]);

@@ -624,6 +624,7 @@ struct FamP {
     R K, invK, n, inv_n, nm1;
     int nm1_int;   // n - 1 when n is an integer in [1, 64], else -1
     R lo, lok, inv_nm1;   // FP32: log2 o*, log2 (o*/K) (root_solve), 1/(n - 1)
+    R u_max;       // FP64: bound of the second-order start (wl_newton)
     R Q, b, qs, ql;   // raw values for the reverse mode
 };
 

@@ -127,35 +127,35 @@ __device__ __forceinline__ double wl_pow(double y, double nm1, const LawP<double
 // second-order change of the root with the overstress,
 //   y (1 + u - a u^2), u = (o - K y - eta g) / S, a = n (n-1)/2 eta g / S,
 //   S = K y + n eta g = y phi',
-// or from y itself where the change is large; without one, from the upper
-// bounds of newton_solve.  The reciprocals are the hardware's estimates
+// while |u| is below u_max: 0.06, beyond n = 10 0.6 / n, since the series is
+// one in n u (at n = 100 and u = 0.06 it ends a third below the root, from
+// where a step leads far above it and 40 iterations do not lead back).
+// Otherwise, and without a root, it starts from the upper bounds of
+// newton_solve, whatever the exponent at most 2^(1/n) above the root.  So
+// at most 6 iterations are needed at n = 10 and 9 at n = 600 (16 and more
+// than 40 from y itself).  The reciprocals are the hardware's estimates
 // (relative error below 1e-7): an error d of the reciprocal leaves an error
 // d step, and the last step is below newton_rtol.  The family's constants
-// are uniform.  1.4-2.1 iterations per active system where a start from the
-// previous root itself takes 2.7-3.3.
+// are uniform.
 template <bool UNI>
 __device__ __forceinline__ double wl_newton(double o, double A, double y, double g, double K, double n, double nm1,
-                                            const LawP<double> &P, int &nnewt)
+                                            double u_max, const LawP<double> &P, int &nnewt)
 {
     const double etaA = P.eta * A;
-    const bool cold = !(y > 0.0);
     const double q = P.eta * g, nq = n * q, Ky = K * y;
     const double rS = __builtin_amdgcn_rcp(Ky + nq);
     const double u = ((o - Ky) - q) * rS;
-    double z = fabs(u) < 0.06 ? y + y * (u - 0.5 * nm1 * nq * rS * u * u) : y;
-    if (__any(!(fabs(u) < 0.06))) {
+    const bool far = !(fabs(u) < u_max);   // no root: u is infinite
+    double z = y + y * (u - 0.5 * nm1 * nq * rS * u * u);
+    if (__any(far)) {
         asm volatile("");
+        // an upper bound is enough: FP32, raised by 1e-5 (newton_solve);
+        // where it underflows o/K is taken, since the logarithm of a
+        // start at 0 would be infinite (0^0 for n = 1: NaN)
         const double yk = o / K;
-        if (!(z < yk)) z = yk;
-        if (__any(cold)) {
-            asm volatile("");
-            // an upper bound is enough: FP32, raised by 1e-5 (newton_solve);
-            // where it underflows o/K is taken, since the logarithm of a
-            // start at 0 would be infinite (0^0 for n = 1: NaN)
-            const float w = (float)o * __builtin_amdgcn_rcpf((float)etaA);
-            const double yc = (double)ex2(lg2(w) * __builtin_amdgcn_rcpf((float)n)) * (1.0 + 1e-5);
-            if (cold) z = yk < yc || !(yc > 0.0) ? yk : yc;
-        }
+        const float w = (float)o * __builtin_amdgcn_rcpf((float)etaA);
+        const double yc = (double)ex2(lg2(w) * __builtin_amdgcn_rcpf((float)n)) * (1.0 + 1e-5);
+        if (far) z = yk < yc || !(yc > 0.0) ? yk : yc;
     }
 #pragma unroll 1
     for (int it = 0; it < 40; ++it) {
@@ -340,7 +340,8 @@ __device__ __forceinline__ void wave_law(const LawP<double> &P, const double *ta
                     if (tw ? on[NSL - 1] : b + lane < ns) {
                         const double os = it->o, o = fabs(os), A = tw ? Atw : 1.0;
                         const double K = tw ? P.ft.K : P.fs.K, nm1 = tw ? P.ft.nm1 : P.fs.nm1;
-                        const double z = wl_newton<UNI>(o, A, it->y, it->g, K, tw ? P.ft.n : P.fs.n, nm1, P, nnewt);
+                        const double z = wl_newton<UNI>(o, A, it->y, it->g, K, tw ? P.ft.n : P.fs.n, nm1,
+                                                        tw ? P.ft.u_max : P.fs.u_max, P, nnewt);
                         it->y = z;
                         double rate = (o - K * z) * P.inv_eta;
                         if (!(P.eta > 0.0)) rate = A * z * wl_pow<UNI>(z, nm1, P);

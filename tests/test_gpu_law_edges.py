@@ -89,3 +89,17 @@ def test_linear_law_at_vanishing_overstress_matches_oracle(strain):
     assert ref.mean_v[-1] > 0.0
     assert _relerr(R["Sigma"], ref.Sigma) < 1e-12
     assert _relerr(s.field("acc_slip").cpu().numpy(), ref.fields["acc_slip"]) < 1e-12
+
+
+# Large exponents: the overstresses of the last stage are 2.5 to 9 times those
+# of the stage before, whose roots the iteration starts from.  A root stops at
+# a relative error of about (n - 1)/2 4.7e-7^2, 2e-11 at n = 200.
+@pytest.mark.parametrize("n,K", [(64.0, 5.0), (100.0, 5.0), (200.0, 25.0)])
+def test_roots_of_large_exponents_match_oracle(n, K):
+    for strain in (2.8e-3, 2.9e-3, 3e-3, 3.1e-3, 3.2e-3):
+        print("case", n, strain, flush=True)
+        w = _crystal([strain], 1e-6, n=n, K=K, c=0.0, d=0.0)
+        s, R, ref = _both(w, 1)
+        v, vr = s.field("acc_slip").cpu().numpy(), ref.fields["acc_slip"]
+        assert (vr.reshape(12, -1).max(axis=1) > 0).sum() >= 6
+        assert _relerr(v, vr) < 1e-10

@@ -133,10 +133,10 @@ __device__ __forceinline__ double wl_pow(double y, double nm1, const LawP<double
 // Otherwise, and without a root, it starts from the upper bounds of
 // newton_solve, whatever the exponent at most 2^(1/n) above the root.  So
 // at most 6 iterations are needed at n = 10 and 9 at n = 600 (16 and more
-// than 40 from y itself).  The reciprocals are the hardware's estimates
-// (relative error below 1e-7): an error d of the reciprocal leaves an error
-// d step, and the last step is below newton_rtol.  The family's constants
-// are uniform.
+// than 40 from y itself).  A step's reciprocal is the hardware's estimate
+// (relative error below 1e-7) refined once: an error d of it leaves an error
+// d step in the root, of which (o - K y)/eta makes up to d of the rate where
+// K y is nearly o.  The family's constants are uniform.
 template <bool UNI>
 __device__ __forceinline__ double wl_newton(double o, double A, double y, double g, double K, double n, double nm1,
                                             double u_max, const LawP<double> &P, int &nnewt)
@@ -161,7 +161,8 @@ __device__ __forceinline__ double wl_newton(double o, double A, double y, double
     for (int it = 0; it < 40; ++it) {
         const double w = etaA * wl_pow<UNI>(z, nm1, P);
         const double phi = (K + w) * z - o;
-        const double step = phi * __builtin_amdgcn_rcp(K + n * w);
+        const double dphi = K + n * w, r = __builtin_amdgcn_rcp(dphi);
+        const double step = phi * fma(r, fma(-dphi, r, 1.0), r);
         z -= step;
         ++nnewt;
         if (fabs(step) <= P.newton_rtol * z) break;

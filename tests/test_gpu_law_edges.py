@@ -103,3 +103,21 @@ def test_roots_of_large_exponents_match_oracle(n, K):
         v, vr = s.field("acc_slip").cpu().numpy(), ref.fields["acc_slip"]
         assert (vr.reshape(12, -1).max(axis=1) > 0).sum() >= 6
         assert _relerr(v, vr) < 1e-10
+
+
+# Overstresses that the Norton term carries to all but 4e-7 and less: the rate
+# is the difference (o - K y) / eta, and the root's first step, about that
+# share of it, is its last.  The rate is then as exact as the reciprocal in
+# that step.  Rounding of o, K y and y, 3e-16 of o, is 2e-9 of the smallest
+# share that counts (1.6e-7 in the middle stages with n = 2): 5e-9.
+@pytest.mark.parametrize("n", [1.0, 2.0])
+@pytest.mark.parametrize("K", [3.0e4, 7.7e4, 1.1e5])
+def test_rates_that_are_a_small_difference_match_oracle(n, K):
+    print("case", n, K, flush=True)
+    y = 100.0 / K if n > 1.0 else 1.0
+    w = _crystal([1e-3], 0.01, systems=rvegen.config_systems(False, 0.0, 0.0), eta=4e-7 * K / y, n=n, K=K, Q=0.0,
+                 c=0.0, d=0.0)
+    s, R, ref = _both(w, 1)
+    assert ref.mean_v[-1] > 1e-10
+    err = _relerr(s.field("acc_slip").cpu().numpy(), ref.fields["acc_slip"])
+    assert err < 5e-9

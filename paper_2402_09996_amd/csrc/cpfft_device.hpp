@@ -1151,7 +1151,11 @@ __device__ __forceinline__ double newton_solve(double o, double A, double etaA, 
 // and the roots a column of LDS.  The law's time is the serial chain of a
 // wave (three waves per SIMD): the FP32 x pass at 128^3 went from 823 to
 // 703 us.  Families without a table (root_ok) start as newton_solve does.
+// Roots below ROOT_MIN, where the step's reciprocal would leave the range of
+// FP32, end as the smaller of ROOT_MIN and o/K: a rate of that size is off
+// by up to as much, and an overstress of 0 gives the rate 0.
 // fam, tab: the family's constants and table; lo: log2 o* for this A.
+constexpr float ROOT_MIN = 1e-36f;
 struct RootIn {
     float o, A, etaA, lo;
     const float *fam, *tab;
@@ -1170,16 +1174,14 @@ __device__ __forceinline__ void root_solve(const RootIn (&q)[NI], const LawP<flo
                                   float(LAW_ROOT_WORDS) - 1.01f);
             const float *t = q[j].tab + (int)u;
             const float Y = fminf(X, X * q[j].fam[2]) - (t[0] + __builtin_amdgcn_fractf(u) * (t[1] - t[0]));
-            // (off zero, where the step below divides: an overstress of no
-            // more than rounding gives the rate 0)
-            y[j] = fmaxf(ex2(Y + (q[j].lo - q[j].fam[4] + q[j].fam[5])), 1e-30f);
+            y[j] = fmaxf(ex2(Y + (q[j].lo - q[j].fam[4] + q[j].fam[5])), ROOT_MIN);
             b[j] = ex2(q[j].fam[1] * Y + q[j].lo);
         }
     } else {
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             const float yk = fdiv(q[j].o, q[j].fam[0]), yc = ex2(lg2(fdiv(q[j].o, q[j].etaA)) * q[j].fam[2]);
-            y[j] = fmaxf(yk < yc ? yk : yc, 1e-30f);
+            y[j] = fmaxf(yk < yc ? yk : yc, ROOT_MIN);
             b[j] = q[j].etaA * ex2(q[j].fam[1] * lg2(y[j]));
         }
     }
@@ -1196,12 +1198,17 @@ __device__ __forceinline__ void root_solve(const RootIn (&q)[NI], const LawP<flo
     }
     if (__any(worst > P.newton_rtol)) {
 #pragma unroll
-        for (int j = 0; j < NI; ++j)
+        for (int j = 0; j < NI; ++j) {
+            // (a root below ROOT_MIN has a first step as large as itself, so
+            // that it comes here; selects keep NaN)
 #pragma unroll 1
             for (int it = 1; it < 40 && fabsf(rel[j]) > P.newton_rtol; ++it) {
+                y[j] = y[j] < ROOT_MIN ? ROOT_MIN : y[j];
                 b[j] = q[j].etaA * ex2(q[j].fam[3] * lg2(y[j])) * y[j];
                 step(j);
             }
+            if (y[j] < ROOT_MIN) y[j] = P.eta > 0.f ? fminf(ROOT_MIN, fdiv(q[j].o, q[j].fam[0])) : ROOT_MIN;
+        }
     }
 #pragma unroll
     for (int j = 0; j < NI; ++j)
@@ -1307,16 +1314,16 @@ __device__ __forceinline__ void rk_stage(const LawP<R> &P, const R e[6], R (&tep
         }
         const R tx = tau - F.c * tal[s];
         if constexpr (sizeof(R) == 4 && !LAG) {
-            // the sign bit of -o is the active bit, shifted in (the systems
-            // end in reverse order), and max(o, 0) keeps the sign of tx
-            // without a select: 128^3 x pass 683 -> 665 us.  An active slip
-            // system has |tx| > r >= 0, so the sign bit of tx is the sign of
-            // the rate.
+            // the sign bit of min(-o, 0) is the active bit, shifted in (the
+            // systems end in reverse order; a NaN is not active), and its
+            // magnitude keeps the sign of tx without a select: 128^3 x pass
+            // 683 -> 665 us.  An active slip system has |tx| > r >= 0, so
+            // the sign bit of tx is the sign of the rate.
             R x = tw ? r - tx : r - fabs(tx);
             if (tw && P.twin_mode && !(Atw > R(0))) x = R(0);
+            x = fminf(x, 0.f);
             act = __builtin_amdgcn_alignbit(act, __float_as_uint(x), 31);
-            const R o = fmaxf(-x, 0.f);
-            W.o[s * W.ls] = tw ? o : copysign(o, tx);
+            W.o[s * W.ls] = tw ? R(fabs(x)) : copysign(x, tx);
             continue;
         }
         const R o = tw ? tx - r : fabs(tx) - r;

@@ -85,3 +85,43 @@ def test_fp32_local_law_matches_oracle(kind, shape, twins):
     assert _relerr(sg.cpu().numpy().reshape(6, nv).T, ref_sig) < 2e-5
     for a, b in ((0, 6), (6, 6 + S), (6 + S, 6 + 2 * S)):
         assert _relerr(st1[:, a:b], ref_st[:, a:b]) < 2e-4
+
+
+def _plain(n, K, eta, shape, strain, seed=7):
+    """Local law without initial resistance and hardening from rest, to
+    deviatoric strains of that size (FP32 values): the solver's and the
+    oracle's state after it and the stress."""
+    C, law = rvegen.config_law()
+    law.slip = dataclasses.replace(law.slip, n=n, K=K, Q=0.0, c=0.0, d=0.0)
+    law.eta = eta
+    w = rvegen.Workload("plain", rvegen.make_rve(shape, 8, 5), rvegen.config_systems(False, 0.0, 0.0), C, law,
+                        rvegen.uniaxial_path(1e-3, 1))
+    rng = np.random.default_rng(seed)
+    nv = int(np.prod(shape))
+    e1 = rng.standard_normal((nv, 6))
+    e1[:, :3] -= e1[:, :3].mean(axis=1, keepdims=True)
+    e1 = (e1 * strain).astype(np.float32)
+    st0 = np.zeros((nv, 30))
+    ref_st, ref_sig = _oracle(w, 0.0 * e1, e1.astype(np.float64), st0, 1e-6, 1)
+
+    def grid(a):
+        return torch.from_numpy(np.ascontiguousarray(a.T.reshape((a.shape[1],) + shape)))
+
+    s = cp.Solver(cp.Problem.from_workload(w), precision="fp32")
+    st1, sg = s.constitutive(grid(0.0 * e1), grid(e1), grid(st0), 1e-6, 1)
+    return (st1.cpu().numpy().reshape(30, nv).T.astype(np.float64), ref_st,
+            sg.cpu().numpy().reshape(6, nv).T.astype(np.float64), ref_sig)
+
+
+# Overstresses down to the least FP32 values: the bound of the other
+# comparisons, beside rounding of o - K y (2e-7 of the stress, over eta) and
+# of the slip (1e-42).
+@pytest.mark.parametrize("n", [1.0, 10.0])
+@pytest.mark.parametrize("strain", [1e-25, 1e-32, 1e-36, 1e-38, 1e-43])
+def test_fp32_vanishing_overstress(n, strain):
+    print("case", n, strain, flush=True)
+    st, ref, sig, ref_sig = _plain(n, 2000.0, 1e4, (2, 4, 4), strain)
+    assert np.isfinite(st).all() and np.isfinite(sig).all()
+    assert np.abs(st[:, 6:18] - ref[:, 6:18]).max() <= (2e-4 * ref[:, 6:18].max() + 1e-42 +
+                                                             2e-7 * np.abs(ref_sig).max() / 1e4 * 1e-6)
+    assert np.abs(sig - ref_sig).max() <= 2e-5 * np.abs(ref_sig).max() + 1e-38

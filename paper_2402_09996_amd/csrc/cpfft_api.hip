@@ -916,8 +916,14 @@ extern "C" int cpf_solver_set_graph(cpf_solver *s, int iters_per_launch)
 // times the square of the step (4.5 rtol^2 at n = 10): 1e-12, two orders
 // below the 1e-10 to which FP64 runs are held.  In FP32 (Halley) it is
 // about (n^2 - 1)/12 times the cube of the step: 1.1e-7 at n = 10, the
-// precision itself.
+// precision itself; for larger exponents the step has to be smaller for the
+// same error (5.2e-4 at n = 100; with that of n = 10, 3e-4 of the rate was
+// off at n = 200).
 constexpr double NEWTON_RTOL_F32 = 2.4e-3;
+static double halley_rtol(double n)
+{
+    return n > 10.0 ? NEWTON_RTOL_F32 * cbrt(99.0 / (n * n - 1.0)) : NEWTON_RTOL_F32;
+}
 constexpr double NEWTON_RTOL_F64 = 4.7e-7;
 
 template <typename R>
@@ -967,11 +973,13 @@ static LawP<R> make_law(const cpf_solver *s)
     for (int k = 0; k < 3; ++k) P.tau0k[k] = R(1e30);
     if (s->law_spec == LAW_TABLE1)
         for (int sy = p.nsys - 1; sy >= 0; --sy) P.tau0k[T1_KIND[sy]] = R(p.tau0[sy]);
-    P.newton_rtol = sizeof(R) == 4 ? R(NEWTON_RTOL_F32) : R(NEWTON_RTOL_F64);
     // one integer exponent n - 1 for every family that has systems (the
     // Newton passes mix the families of different lanes)
     bool has[2] = {false, false};
     for (int sy = 0; sy < p.nsys; ++sy) has[p.fam[sy] ? 1 : 0] = true;
+    P.newton_rtol = R(NEWTON_RTOL_F64);
+    if (sizeof(R) == 4)
+        P.newton_rtol = R(halley_rtol(std::max(has[0] ? p.law[0].n : 0.0, has[1] ? p.law[1].n : 0.0)));
     P.root_ok = (!has[0] || s->root_ok[0]) && (!has[1] || s->root_ok[1]);
     P.nm1_uni = -1;
     for (int f = 0; f < 2; ++f) {

@@ -1146,8 +1146,9 @@ __device__ __forceinline__ double newton_solve(double o, double A, double etaA, 
 // crossover and 1/4 above, where its curvature is of that scale).  That
 // leaves y within 2.1e-3 of the root at n = 10 (3.4e-3 at n = 50), so that
 // one step of Halley's method ends nearly every solve (1.000 steps per
-// solve at n = 10): the lanes of a pass are done together.  Warm starts
-// took 1.88 Newton steps on average and 3 or more in some lane of a pass,
+// solve at n = 10; with the closer stop of larger exponents up to 1.6 next
+// above the crossover at n = 50): the lanes of a pass are done together.
+// Warm starts took 1.88 Newton steps on average and 3 or more in some lane of a pass,
 // and the roots a column of LDS.  The law's time is the serial chain of a
 // wave (three waves per SIMD): the FP32 x pass at 128^3 went from 823 to
 // 703 us.  Families without a table (root_ok) start as newton_solve does.

@@ -113,6 +113,22 @@ def _plain(n, K, eta, shape, strain, seed=7):
             sg.cpu().numpy().reshape(6, nv).T.astype(np.float64), ref_sig)
 
 
+# Overstresses a tenth to a third above K, of which the rate is that share:
+# rounding of the overstress, up to 2e-6 of it, is 2e-5 of the rate, and the
+# root's 1.1e-7 adds 1e-6 whatever the exponent.
+@pytest.mark.parametrize("n", [50.0, 100.0, 200.0, 400.0])
+def test_fp32_roots_of_large_exponents_match_oracle(n):
+    print("case", n, flush=True)
+    K, eta = 60.0, 10.0
+    st, ref, _, _ = _plain(n, K, eta, (8, 16, 16), 3e-4)
+    v, vr = st[:, 6:18], ref[:, 6:18]
+    g = np.maximum(vr, 0.0) * 6e6           # the last stage's: the others are below K
+    share = (g ** (1.0 / n) * K + eta * g) / K
+    sel = (share > 1.1) & (share < 1.35)
+    assert sel.sum() > 500
+    assert np.abs(v[sel] / vr[sel] - 1.0).max() < 3e-5
+
+
 # Overstresses down to the least FP32 values: the bound of the other
 # comparisons, beside rounding of o - K y (2e-7 of the stress, over eta) and
 # of the slip (1e-42).

@@ -217,7 +217,8 @@ typedef struct cpf_step_out {
     double sig_eq_of_mean, mean_sig_eq, mean_v, mean_f;
     double err_eq, err_bc;
     double n_active;  /* work counters over the step's iterations: system  */
-    double n_newton;  /* rate evaluations above yield, Newton iterations   */
+    double n_newton;  /* rate evaluations above yield, and the steps of
+                         their root solves (FP64 Newton, FP32 Halley)      */
     int iters;        /* constitutive evaluations (fixed-point iterations) */
     int status;       /* CPF_OK, CPF_E_NOT_CONVERGED or CPF_E_NAN          */
     int stagnated;    /* 1: ended by the stalled-residual acceptance

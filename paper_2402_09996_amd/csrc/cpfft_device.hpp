@@ -1162,9 +1162,10 @@ struct RootIn {
     const float *fam, *tab;
 };
 // NI systems at once, so that their chains of loads and hardware powers
-// overlap.
-template <int NI>
-__device__ __forceinline__ void root_solve(const RootIn (&q)[NI], const LawP<float> &P, float (&y)[NI], float (&g)[NI])
+// overlap; nnewt counts the steps of those that are counted(j).
+template <int NI, typename Counted>
+__device__ __forceinline__ void root_solve(const RootIn (&q)[NI], const LawP<float> &P, float (&y)[NI], float (&g)[NI],
+                                           int &nnewt, Counted counted)
 {
     float b[NI], rel[NI], worst = 0.f;
     if (P.root_ok) {
@@ -1207,6 +1208,7 @@ __device__ __forceinline__ void root_solve(const RootIn (&q)[NI], const LawP<flo
                 y[j] = y[j] < ROOT_MIN ? ROOT_MIN : y[j];
                 b[j] = q[j].etaA * ex2(q[j].fam[3] * lg2(y[j])) * y[j];
                 step(j);
+                nnewt += counted(j);
             }
             if (y[j] < ROOT_MIN) y[j] = P.eta > 0.f ? fminf(ROOT_MIN, fdiv(q[j].o, q[j].fam[0])) : ROOT_MIN;
         }
@@ -1425,7 +1427,8 @@ __device__ __forceinline__ void rk_stage(const LawP<R> &P, const R e[6], R (&tep
                         q[j].lo -= lg2(q[j].A) * q[j].fam[7];
                     }
             }
-            root_solve<NI>(q, P, y, g);
+            // (the first step of every solve is counted at the end)
+            root_solve<NI>(q, P, y, g, nnewt, [&](int j) { return j == 0 || idx + j * nlanes < total ? 1 : 0; });
 #pragma unroll
             for (int j = 0; j < NI; ++j) {
                 if (W.y) W.y[it[j] - (int)threadIdx.x] = y[j];
@@ -1479,7 +1482,7 @@ __device__ __forceinline__ void rk_stage(const LawP<R> &P, const R e[6], R (&tep
                 const RootIn q[1] = {{R(fabs(os)), A, etaA, tw ? fam[4] - lg2(A) * fam[7] : fam[4], fam,
                                       W.fam + 2 * LAW_FAM_WORDS + (tw ? LAW_ROOT_WORDS : 0)}};
                 R y1[1], g1[1];
-                root_solve<1>(q, P, y1, g1);
+                root_solve<1>(q, P, y1, g1, nnewt, [](int) { return 1; });
                 y = y1[0];
                 g = g1[0];
                 ++nnewt;

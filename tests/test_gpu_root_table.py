@@ -141,3 +141,22 @@ def test_fp32_vanishing_overstress(n, strain):
     assert np.abs(st[:, 6:18] - ref[:, 6:18]).max() <= (2e-4 * ref[:, 6:18].max() + 1e-42 +
                                                              2e-7 * np.abs(ref_sig).max() / 1e4 * 1e-6)
     assert np.abs(sig - ref_sig).max() <= 2e-5 * np.abs(ref_sig).max() + 1e-38
+
+
+# n_newton counts the steps of the root solves: two for each with an exponent
+# of 1, where they start from the smaller of o/K and o/eta and a second step
+# finds nothing left; one, but for few, from the table.  Groups of 64 lanes
+# that are full and partly empty.
+@pytest.mark.parametrize("shape", [(2, 2, 4), (3, 3, 3), (4, 8, 8)])
+def test_fp32_step_count(shape):
+    for n, K, lo, hi in ((1.0, 2000.0, 2.0, 2.0), (10.0, 10.0, 1.0, 1.05)):
+        print("case", shape, n, flush=True)
+        C, law = rvegen.config_law()
+        law.slip = dataclasses.replace(law.slip, n=n, K=K)
+        path = rvegen.LoadPath(t=np.array([0.0, 0.4]), strain_ctrl=np.ones((1, 6), np.uint8),
+                               target=4e-3 * np.array([[1.0, -0.45, -0.55, 0.12, -0.2, 0.31]]))
+        w = rvegen.Workload("count", rvegen.make_rve(shape, 1, 5), rvegen.config_systems(False), C, law, path)
+        R = cp.Solver(cp.Problem.from_workload(w), precision="fp32", tol=1e-4, rk4_M=4).run(w.path)
+        assert R["n_active"][0] > 0
+        ratio = R["n_newton"][0] / R["n_active"][0]
+        assert lo <= ratio <= hi

@@ -1387,8 +1387,6 @@ __device__ __forceinline__ void rk_stage(const LawP<R> &P, const R e[6], R (&tep
     const uint64_t ex = __ballot(1);
     const int nlanes = __popcll(ex);
     const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(ex >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ex, 0u));
-    [[maybe_unused]] R *const o_wave = W.o - lane;   // column of lane l: o_wave + l
-    [[maybe_unused]] R *const y_wave = W.y - lane;
     if constexpr (sizeof(R) == 4) {
         // up to three items per lane at once: the chain of a pass (item,
         // overstress, table, powers, reciprocals) is several times as long as
@@ -1444,6 +1442,8 @@ __device__ __forceinline__ void rk_stage(const LawP<R> &P, const R e[6], R (&tep
         if (base + rank < total) pass(std::integral_constant<int, 1>(), base + rank);
         nnewt += cnt;
     } else {
+        R *const o_wave = W.o - lane;   // column of lane l: o_wave + l
+        R *const y_wave = W.y - lane;
         for (int base = 0; base < total; base += nlanes) {
             const int idx = base + rank;
             if (idx < total) {

@@ -413,8 +413,9 @@ __global__ __launch_bounds__(256, (xpass_min_blocks<R, SPEC>())) void k_xpass_it
     if (spec_in && tid < d.tpbx)
         load_halfspec_pairs(d.spec, buf, d.nx, d.ny, d.nz, d.nkx, d.nhp, d.L, li, x, y, z, valid);
     // the voxel's inputs are on their way while the lines are transformed
-    // (a 256-wide FP32 grid with few substeps: 117 -> 113 ms per solve)
-    const R *base = first ? eps_n : eps_k;
+    // (a 256-wide FP32 grid with few substeps: 117 -> 113 ms per solve);
+    // threads without one read voxel 0 of arrays that this pass does not write
+    const R *base = first || !valid ? eps_n : eps_k;
     const long vin = valid ? vox : 0;
     const int lab = d.labels[vin];
     R e1[6], e0[6];

@@ -33,7 +33,7 @@ FP64_PEAK_TFLOPS = 78.6
 # HBM bytes per launch of the x pass (the dominant kernel) at 128^3 FP32,
 # from rocprofv3 FETCH_SIZE / WRITE_SIZE scaled by a 1 GiB copy (factors
 # 0.5 and 1.0); valid only for the library sources they were taken on.
-XPASS_TRAFFIC = {"src": "feb78cbf0f56681f", "read_bytes": 479.4e6, "write_bytes": 420.4e6}
+XPASS_TRAFFIC = {"src": "4e3679d2d7160581", "read_bytes": 479.1e6, "write_bytes": 420.3e6}
 
 
 def library_source_hash() -> str:
@@ -53,7 +53,7 @@ def law_flops(S: int, n_twin: int, M: int, nvox: int, n_active: float, n_newton:
     breakdown is documented with the kernel."""
     per_rate = 114 + 51 * S + 2 * n_twin
     per_active = 10
-    per_newton = 16
+    per_newton = 16                          # a Newton (FP64) or Halley (FP32) step
     per_voxel_fixed = 450 + 12 + 30          # frame rotations, strain update, sums
     return nvox * (4 * M * per_rate + per_voxel_fixed) + n_active * per_active + n_newton * per_newton
 

@@ -519,11 +519,14 @@ static void pass_grids(cpf_solver *s)
 // Lines per block of the cooperative law.  A block's four waves take its
 // groups of 16 voxels in turn, so its time goes by the groups of one wave,
 // plus about half a group for the transforms and rotations; about 768 blocks
-// are resident (three per CU).  Small problems gain from few voxels per block
-// (every CU has one; fewer than 64 leave waves without a group), large ones
-// from many, and lines that are no multiple of 64 leave waves idle; the count
-// with the least time is taken (FP64 x pass, 256 voxels and the chosen: 24^3
-// 77 / 58 us, 32^3 91 / 63, 64^3 373 / 350), of equal ones the smallest,
+// are resident (three per CU; the estimate leaves out that two are with lines
+// of 192 points and more, whose twiddles take the LDS of the third, and with
+// exponents that are no common integer).  Small problems gain from few voxels
+// per block (every CU has one; below 64, one line of 48 or two of 24, waves
+// are left without a group, and fewer lines than that are not tried), large
+// ones from many, and lines that are no multiple of 64 leave waves idle; the
+// count with the least time is taken (FP64 x pass, 256 voxels and the chosen:
+// 24^3 77 / 58 us, 32^3 91 / 63, 64^3 373 / 350), of equal ones the smallest,
 // which spreads best over the CUs (48^3: 4 lines 190, 3 lines 170 us).  By
 // the member's own grid alone, so that it is computed the same in every
 // batch.

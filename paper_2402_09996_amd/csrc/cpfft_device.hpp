@@ -646,8 +646,9 @@ struct LawP {
     R newton_rtol;
     int nm1_uni;          // n - 1 when every family present has the same integer
                           // n in [1, 64] (a wave-uniform exponent), else -1
-    R tau0k[3];           // FP32 LAW_TABLE1: initial resistance per kind of
-                          // Table 1 system (ordinary, superdislocation, twin)
+    R tau0k[3];           // LAW_TABLE1 (FP32 and the four-lane law): initial
+                          // resistance per kind of Table 1 system (ordinary,
+                          // superdislocation, twin)
     int root_ok;          // FP32: the families present have tables of root_solve
     R root[sizeof(R) == 4 ? 2 * LAW_ROOT_WORDS : 1];   // FP32: slip, twin (root_solve)
 };
@@ -956,7 +957,7 @@ __device__ __forceinline__ void law_fence() { asm volatile("" ::: "memory"); }
 template <typename R>
 struct LawLds {
     R *o;       // [NS] overstress, then rate
-    R *y;       // [NS] Newton roots (FP64: warm starts; FP32: only if kept)
+    R *y;       // [NS] roots (FP64: warm starts; FP32: null unless kept)
     R *e;       // [12] start and end strain of the load step
     R *fam;     // [2][LAW_FAM_WORDS] Norton constants of the slip and twin
                 // families, one copy per block
@@ -1148,13 +1149,13 @@ __device__ __forceinline__ double newton_solve(double o, double A, double etaA, 
 // one step of Halley's method ends nearly every solve (1.000 steps per
 // solve at n = 10; with the closer stop of larger exponents up to 1.6 next
 // above the crossover at n = 50): the lanes of a pass are done together.
-// Warm starts took 1.88 Newton steps on average and 3 or more in some lane of a pass,
-// and the roots a column of LDS.  The law's time is the serial chain of a
-// wave (three waves per SIMD): the FP32 x pass at 128^3 went from 823 to
-// 703 us.  Families without a table (root_ok) start as newton_solve does.
+// Warm starts took 1.88 Newton steps on average and 3 or more in some lane
+// of a pass, and the roots a column of LDS: the FP32 x pass at 128^3, bound by
+// VALU issue, went from 823 to 703 us.  Families without a table (root_ok)
+// start as newton_solve does.
 // Roots below ROOT_MIN, where the step's reciprocal would leave the range of
-// FP32, end as the smaller of ROOT_MIN and o/K: a rate of that size is off
-// by up to as much, and an overstress of 0 gives the rate 0.
+// FP32, end as the smaller of ROOT_MIN and o/K: an overstress below ROOT_MIN K
+// gives the rate 0.
 // fam, tab: the family's constants and table; lo: log2 o* for this A.
 constexpr float ROOT_MIN = 1e-36f;
 struct RootIn {

@@ -508,7 +508,8 @@ __global__ __launch_bounds__(256, (xpass_min_blocks<R, SPEC>())) void k_xpass_it
 // one voxel each; in between its waves integrate the voxels in groups of 16,
 // the strains handed over in LDS.  LDS: the transform lines (idle during the
 // law, when the waves' root-solve lists lie there), H, the strain rows, the
-// twiddles.
+// twiddles: 51 KB and 16 bytes per point of a line, of which a CU holds three
+// up to lines of 162 points and two from 192 on.
 // ---------------------------------------------------------------------------
 static_assert(4 * WL_LIST_BYTES >= 3 * 256 * sizeof(C2<double>), "the transform lines exceed the lists");
 constexpr size_t xwave_lds_bytes(int nx)
@@ -547,8 +548,8 @@ __device__ __forceinline__ void wl_leave(const LawP<double> &P, const double *rc
 }
 
 // Blocks per CU that the registers are limited for: three (168 registers; two
-// blocks with 220 took 2.75 ms at 128^3 against 2.22); two with the software
-// power (213).
+// blocks with 220 took 2.75 ms at 128^3 against 2.22), whether or not the LDS
+// of the line length holds them; two with the software power (213).
 template <bool UNI>
 constexpr int xwave_min_blocks()
 {
@@ -1007,6 +1008,10 @@ __global__ __launch_bounds__(Z_THREADS) void k_zpass_green(const RveDev<R> *__re
 // ---------------------------------------------------------------------------
 constexpr int FX_THREADS = 256;   // threads of the fixed-length y and z blocks
 
+// The lengths of the solver's configurations and 16, the smallest grids'
+// (16^3 in FP64, launch-bound: z pass 7.6 us with the general plan, 5.6 with
+// its own).  Each length is one more instantiation in every switch below; for
+// 24 and the lengths with more factors of three it was not tried.
 __host__ __device__ constexpr bool fixed_len(int n)
 {
     return n == 16 || n == 32 || n == 48 || n == 64 || n == 96 || n == 128 || n == 256;

@@ -15,15 +15,15 @@
 // keeps 6 + 2 S state values, three RK4 copies of them and Newton columns
 // per lane: 338 registers and 106 KB of LDS per block, one wave per SIMD,
 // VALU 49 % busy.  Here a lane holds a quarter of the systems: 168 registers
-// and 53 KB, three waves per SIMD, VALU 69 % and matrix units 12 % busy (the
-// FP64 matrix and vector instructions share the SIMD's FP64 units: measured
-// together they take the sum of their times, so the matrix form saves the
-// exchange between lanes, not arithmetic).  128^3, 16 systems, 4 substeps,
-// per launch over four load steps: 3882 us before, 2195 now; 64^3 847 / 600,
-// 16^3 (12 systems, 10-16 substeps) 226 / 79.  FP32 keeps a lane per voxel:
-// three of its blocks run per CU as it is, and the exchange between lanes
-// here adds instructions (128^3: 822 us with its Newton solves of that time,
-// against 1169).
+// and 53 KB at 128 points, three waves per SIMD, VALU 58 % and matrix units
+// 14 % busy at 128^3 (the FP64 matrix and vector instructions share the SIMD's
+// FP64 units: measured together they take the sum of their times, so the
+// matrix form saves the exchange between lanes, not arithmetic).  128^3, 16
+// systems, 4 substeps, per launch over four load steps: 3882 us before, 2195
+// now; 64^3 847 / 600, 16^3 (12 systems, 10-16 substeps) 226 / 79.  FP32 keeps
+// a lane per voxel: three of its blocks run per CU as it is, and the exchange
+// between lanes here adds instructions (128^3: 822 us with its Newton solves
+// of that time, against 1169).
 #pragma once
 #include "cpfft_device.hpp"
 
